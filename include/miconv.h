@@ -170,8 +170,10 @@ long conv2d_workspace_bytes(int N, int C, int H, int W, int K, int R, int S, int
  * order its kernel reads, all inside `ws`: the fastest single-call plans.
  * The library keeps no reference to ws after the call's kernels are
  * enqueued; they use it until they complete on `stream`, so concurrent calls
- * need distinct workspaces.  Too small or unaligned: MICONV_ERR_WORKSPACE,
- * nothing enqueued.  Everything else as conv2d_fwd_ex. */
+ * need distinct workspaces.  A workspace below conv2d_workspace_bytes that
+ * still holds a slower plan's scratch (fp32 layers that would run on a split
+ * copy of x) runs that plan; too small for any, or unaligned:
+ * MICONV_ERR_WORKSPACE, nothing enqueued.  Everything else as conv2d_fwd_ex. */
 int conv2d_fwd_ws(int N, int C, int H, int W, int K, int R, int S, int stride, int pad, int groups,
                   int dtype, int algo, const void *x, const void *w, const float *bias, const float *res,
                   float *y, long y_image_stride, int relu, void *ws, size_t ws_bytes, void *stream);

@@ -181,7 +181,7 @@ static int resolve_pool(int kind, int N, int C, int H, int W, int K, int R, int 
 
 int resolve(int kind, int algo, int mode, int N, int C, int H, int W, int K, int R, int S, int stride,
             int pad, int groups, const void *x, const void *w, const float *bias, float *y,
-            int relu, Resolved *out, int layout)
+            int relu, Resolved *out, int layout, size_t ws_limit)
 {
     if (kind == OP_MAXPOOL_BF16_NHWC || kind == OP_MAXPOOL_F32)
         return resolve_pool(kind, N, C, H, W, K, R, S, stride, pad, x, y, out);
@@ -284,11 +284,26 @@ int resolve(int kind, int algo, int mode, int N, int C, int H, int W, int K, int
         if (r.impl == IMPL_IGEMM) {
             // The wave kernel serves every size it can address (measured faster
             // than the LDS-tiled kernel from batch-1 ResNet layers to VGG-16 at
-            // batch 32), unless the caller forced the tiled one.
+            // batch 32), unless the caller forced the tiled one or, below, the
+            // layer is worth splitting for the bf16 matrix cores.
             if (algo != MICONV_ALGO_IGEMM && wave_fits(r.p))
                 r.impl = IMPL_WAVE;
             else
                 r.plan = plan_igemm_f32(r.p, cus, max_splits);
+        }
+        if (algo == MICONV_ALGO_AUTO && scratch && r.impl == IMPL_WAVE && split3_fits(r.p)) {
+            // The reduction runs on the bf16 matrix cores where that pays; it
+            // takes more scratch than the other plans, so a smaller workspace
+            // keeps those.
+            Resolved sp = r;
+            sp.impl = IMPL_SPLIT_F32;
+            sp.pack_per_call = !(mode & MODE_PREPACK);
+            sp.splan = plan_split3(r.p, cus, max_splits, sp.pack_per_call);
+            sp.wlayout = WL_SPLIT3;
+            if (split3_pays(r.p, sp.splan, !sp.pack_per_call) && workspace_bytes(sp) <= ws_limit) {
+                *out = sp;
+                return MICONV_OK;
+            }
         }
         if (r.impl == IMPL_WAVE) {
             if (!wave_fits(r.p)) return MICONV_ERR_UNSUPPORTED;
@@ -350,6 +365,7 @@ size_t packed_bytes(const Resolved &r)
 {
     if (r.wlayout == WL_STEM) return stem_packed_bytes(r.p);
     if (r.wlayout == WL_WAVE) return wave_packed_floats(r.p) * sizeof(float);
+    if (r.wlayout == WL_SPLIT3) return split3_packed_bytes(r.p);
     const size_t elem = r.kind == OP_DENSE_BF16 ? sizeof(uint16_t) : sizeof(float);
     return (size_t)r.p.K * r.p.Cg * r.p.R * r.p.S * elem;
 }
@@ -382,6 +398,7 @@ hipError_t launch_pack(const Resolved &r, void *dst, hipStream_t st)
         return launch_pack_stem(r.p, static_cast<const uint16_t *>(r.w), static_cast<uint16_t *>(dst), st);
     if (r.wlayout == WL_WAVE)
         return launch_pack_wave(r.p, static_cast<const float *>(r.w), static_cast<float *>(dst), st);
+    if (r.wlayout == WL_SPLIT3) return launch_pack_split3(r.p, static_cast<const float *>(r.w), dst, st);
     const size_t elem = r.kind == OP_DENSE_BF16 ? sizeof(uint16_t) : sizeof(float);
     const int cblk = r.wlayout == WL_KRSC_BLOCK ? 64 : 0;   // (block, r, s, c) order
     return launch_pack_krsc(r.p, r.w, dst, elem, st, cblk);
@@ -390,7 +407,7 @@ hipError_t launch_pack(const Resolved &r, void *dst, hipStream_t st)
 hipError_t enqueue(const Resolved &r0, float *ws, hipStream_t st, const LaunchHook *hook)
 {
     Resolved r = r0;
-    // workspace layout: [packed filters (per-call packing)][channel-last x][split partials]
+    // workspace layout: [packed filters (per-call packing)][copy of x][split partials]
     char *cursor = reinterpret_cast<char *>(ws);
     if (r.pack_per_call) {
         if (hook) {
@@ -406,6 +423,11 @@ hipError_t enqueue(const Resolved &r0, float *ws, hipStream_t st, const LaunchHo
     if (r.impl == IMPL_NHWC_BF16) {
         xcl = reinterpret_cast<uint16_t *>(cursor);
         cursor += round256(r.nplan.xcl_bytes);
+    }
+    if (r.impl == IMPL_SPLIT_F32) {
+        float *partials = reinterpret_cast<float *>(cursor + round256(r.splan.xs_bytes));
+        return launch_split3(r.p, r.splan, static_cast<const float *>(r.x), static_cast<const float *>(r.w), r.wk,
+                             r.bias, r.y, cursor, partials, st, hook);
     }
     ws = reinterpret_cast<float *>(cursor);
     const void *wkern = r.wk ? r.wk : r.w;
@@ -455,6 +477,7 @@ size_t workspace_bytes(const Resolved &r)
     if (r.impl == IMPL_IGEMM || r.impl == IMPL_IGEMM_BF16) b = r.plan.ws_bytes;
     if (r.impl == IMPL_WAVE) b = r.wplan.ws_bytes;
     if (r.impl == IMPL_NHWC_BF16) b = round256(r.nplan.xcl_bytes) + r.nplan.partial_bytes;
+    if (r.impl == IMPL_SPLIT_F32) b = round256(r.splan.xs_bytes) + r.splan.partial_bytes;
     if (r.pack_per_call) b = round256(b) + round256(packed_bytes(r));
     return b;
 }
@@ -464,6 +487,7 @@ void describe(const Resolved &r, char *buf, int len, int *launches)
     if (r.pack_per_call) {
         const int n = r.wlayout == WL_STEM ? snprintf(buf, len, "pack_stem_kernel + ")
                       : r.wlayout == WL_WAVE ? snprintf(buf, len, "pack_wave_kernel + ")
+                      : r.wlayout == WL_SPLIT3 ? snprintf(buf, len, "split3_pack_kernel + ")
                                                : snprintf(buf, len, "pack_krsc_kernel<%s> + ",
                                      r.kind == OP_DENSE_BF16 ? "unsigned short" : "float");
         if (n > 0 && n < len) {
@@ -481,6 +505,7 @@ void describe_kernel(const Resolved &r, char *buf, int len, int *launches)
     case IMPL_DW: describe_dwconv(r.p, buf, len, launches); break;
     case IMPL_IGEMM: describe_igemm_f32(r.p, r.plan, buf, len, launches); break;
     case IMPL_WAVE: describe_wave_f32(r.p, r.wplan, buf, len, launches); break;
+    case IMPL_SPLIT_F32: describe_split3(r.p, r.splan, buf, len, launches); break;
     case IMPL_IGEMM_BF16: describe_igemm_bf16(r.p, r.plan, r.bfast, r.bva, buf, len, launches); break;
     case IMPL_NHWC_BF16: describe_nhwc_bf16(r.p, r.nplan, buf, len, launches); break;
     case IMPL_STEM_BF16: describe_stem_bf16(buf, len, launches); break;
@@ -572,11 +597,11 @@ namespace miconv {
 // output image stride, planned for `mode`.
 int resolve_ex(int mode, int N, int C, int H, int W, int K, int R, int S, int stride, int pad,
                int groups, int dtype, int algo, const void *x, const void *w, const float *bias,
-               const float *res, float *y, long y_image_stride, int relu, Resolved *r)
+               const float *res, float *y, long y_image_stride, int relu, Resolved *r, size_t ws_limit)
 {
     if (dtype != 0 && dtype != 1) return MICONV_ERR_UNSUPPORTED;
     int rc = resolve(dtype == 1 ? OP_DENSE_BF16 : OP_DENSE_F32, algo, mode, N, C, H, W, K, R, S, stride,
-                     pad, groups, x, w, bias, y, relu, r);
+                     pad, groups, x, w, bias, y, relu, r, 0, ws_limit);
     if (rc == MICONV_OK) rc = set_output_stride(*r, y_image_stride);
     if (rc == MICONV_OK) rc = set_residual(*r, res);
     return rc;
@@ -633,8 +658,9 @@ int conv2d_fwd_ws(int N, int C, int H, int W, int K, int R, int S, int stride, i
                   float *y, long y_image_stride, int relu, void *ws, size_t ws_bytes, void *stream)
 {
     Resolved r;
+    const size_t have = ws && (uintptr_t)ws % 256 == 0 ? ws_bytes : 0;
     const int rc = resolve_ex(MODE_SCRATCH, N, C, H, W, K, R, S, stride, pad, groups, dtype, algo, x, w,
-                              bias, res, y, y_image_stride, relu, &r);
+                              bias, res, y, y_image_stride, relu, &r, have);
     return rc != MICONV_OK ? rc : run(r, ws, ws_bytes, static_cast<hipStream_t>(stream));
 }
 

@@ -1,8 +1,8 @@
 // Dense conv2d in fp32 as an implicit GEMM in which every wavefront feeds
 // the matrix cores straight from global memory: no LDS staging and no
-// barriers in the main loop.  It serves every fp32 dense layer whose tensors
-// it can address with 32-bit offsets, from batch-1 ResNet layers to VGG-16
-// at batch 32.
+// barriers in the main loop.  It serves the fp32 dense layers whose tensors
+// it can address with 32-bit offsets, except those with scratch that are
+// large enough for the split kernels (conv_split_f32.hip).
 //
 // Why: at batch 1 the layers of ResNet-50 / MobileNet have N*P*Q = 49..12544
 // output pixels, so an LDS-staged tile kernel runs few chunks per

@@ -175,6 +175,26 @@ hipError_t launch_wave_f32(const ConvProblem &p, const WavePlan &plan, const flo
                            hipStream_t st, const LaunchHook *hook = nullptr);
 void describe_wave_f32(const ConvProblem &p, const WavePlan &plan, char *buf, int len,
                        int *launches);
+// fp32 layers bound by the fp32 MFMA rate: x and filters split exactly into
+// three bf16 parts, six bf16 MFMAs per product (needs a workspace for the
+// split channel-last copy of x).
+struct SplitPlan {
+    int tile;             // index into the tile table
+    int splits, per_split;   // reduction splits, chunks per split
+    size_t xs_bytes;      // the split copy of x
+    size_t partial_bytes;
+    double us;            // what the planner's model expects it to take
+};
+bool split3_fits(const ConvProblem &p);
+SplitPlan plan_split3(const ConvProblem &p, int num_cus, int max_splits, bool pack_per_call);
+bool split3_pays(const ConvProblem &p, const SplitPlan &plan, bool packed);   // against the wave kernel
+size_t split3_packed_bytes(const ConvProblem &p);
+hipError_t launch_pack_split3(const ConvProblem &p, const float *w, void *packed, hipStream_t st);
+// x, w: the fp32 tensors as given; packed: launch_pack_split3's filters.
+hipError_t launch_split3(const ConvProblem &p, const SplitPlan &plan, const float *x, const float *w,
+                         const void *packed, const float *bias, float *y, void *xs, float *partials, hipStream_t st,
+                         const LaunchHook *hook = nullptr);
+void describe_split3(const ConvProblem &p, const SplitPlan &plan, char *buf, int len, int *launches);
 // bf16 inputs, fp32 accumulation (v_mfma_f32_32x32x16_bf16).
 IgemmPlan plan_igemm_bf16(const ConvProblem &p, int num_cus, int max_splits);
 bool bf16_fast_1x1(const ConvProblem &p, const void *x);
@@ -250,7 +270,8 @@ enum Impl {
     IMPL_NHWC_BF16 = 5,
     IMPL_STEM_BF16 = 6,
     IMPL_POOL_NHWC = 7,
-    IMPL_POOL_F32 = 8
+    IMPL_POOL_F32 = 8,
+    IMPL_SPLIT_F32 = 9
 };
 // What a call may use besides its tensors.
 enum PlanMode {
@@ -266,7 +287,8 @@ enum WeightLayout {
     WL_STEM = 1,        // bf16 7x7 stem: tap pairs
     WL_WAVE = 2,        // fp32 wave kernel: wavefront load order
     WL_KRSC = 3,        // [K][R][S][C/groups]
-    WL_KRSC_BLOCK = 4   // KRSC per block of 64 channels
+    WL_KRSC_BLOCK = 4,  // KRSC per block of 64 channels
+    WL_SPLIT3 = 5       // three bf16 parts per value, by 64-filter tile and reduction chunk
 };
 struct Resolved {
     ConvProblem p;
@@ -278,15 +300,19 @@ struct Resolved {
     WavePlan wplan;     // IMPL_WAVE only
     bool bfast, bva;    // IMPL_IGEMM_BF16: vectorised 1x1 loader, 16-byte filter loads
     NhwcPlan nplan;     // IMPL_NHWC_BF16 only
+    SplitPlan splan;    // IMPL_SPLIT_F32 only
     bool pack_per_call; // enqueue packs the filters into the workspace first
     const void *wk;     // filters the conv kernel reads when they were packed ahead (else w)
     const void *x, *w;
     const float *bias;
     float *y;
 };
+// ws_limit: the scratch bytes the caller has.  A plan that is only faster, not
+// needed, is not chosen beyond it.
+constexpr size_t kNoLimit = ~(size_t)0;
 int resolve(int kind, int algo, int mode, int N, int C, int H, int W, int K, int R, int S, int stride,
             int pad, int groups, const void *x, const void *w, const float *bias, float *y,
-            int relu, Resolved *out, int layout = 0);
+            int relu, Resolved *out, int layout = 0, size_t ws_limit = kNoLimit);
 // resolve() for tensors at 256-byte boundaries (w may be null: a stand-in).
 int resolve_aligned(int N, int C, int H, int W, int K, int R, int S, int stride, int pad, int groups,
                     int dtype, int algo, int mode, const void *w, Resolved *out);
@@ -294,7 +320,7 @@ int resolve_aligned(int N, int C, int H, int W, int K, int R, int S, int stride,
 // fp32, 1 bf16), planned for `mode`.
 int resolve_ex(int mode, int N, int C, int H, int W, int K, int R, int S, int stride, int pad,
                int groups, int dtype, int algo, const void *x, const void *w, const float *bias,
-               const float *res, float *y, long y_image_stride, int relu, Resolved *r);
+               const float *res, float *y, long y_image_stride, int relu, Resolved *r, size_t ws_limit = kNoLimit);
 // Enqueue r on a workspace of ws_bytes bytes, 256-byte aligned (ws may be null
 // when workspace_bytes(r) is 0); returns a miconv_status.
 int run(const Resolved &r, void *ws, size_t ws_bytes, hipStream_t st);

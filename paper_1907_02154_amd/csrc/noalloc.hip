@@ -50,7 +50,7 @@ extern "C" int conv2d_fwd_noalloc(int N, int C, int H, int W, int K, int R, int 
 {
     miconv::Resolved r;
     int rc = miconv::resolve_ex(miconv::MODE_SCRATCH, N, C, H, W, K, R, S, stride, pad, groups, dtype, algo,
-                                x, w, bias, res, y, y_image_stride, relu, &r);
+                                x, w, bias, res, y, y_image_stride, relu, &r, kScratchBytes);
     if (rc != MICONV_OK) return rc;
     const size_t need = miconv::workspace_bytes(r);
     if (need > kScratchBytes) return MICONV_ERR_WORKSPACE;   // beyond the fixed scratch
