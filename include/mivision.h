@@ -58,12 +58,12 @@ int vision_scan_i32(int rows, long n, const int32_t *x, int32_t *y, int exclusiv
  * largest key first).  Equal keys keep their order (stable); -0 and +0 are
  * equal; NaN keys come last in either order.  Positions at or past
  * offsets[segments] belong to no segment and get -1.
- * The flattened array is cut into equal blocks of 2048 elements, each block
- * is sorted in LDS by (segment, key, position), then sorted runs are merged
- * pairwise, doubling the run length per pass, each work-group producing
- * 2048 outputs of a merge at the split points of its merge path; a pair
- * whose two runs meet at a segment boundary is already in order and is
- * copied.  Errors: MICONV_ERR_NULL, MICONV_ERR_SHAPE (n < 1, segments < 1),
+ * The flattened array is cut into equal blocks of 2048 to 8192 elements, each sorted
+ * in LDS by (segment, key, position); the parts of segments that span blocks
+ * are then merged pairwise, doubling the parts' length per pass, each
+ * work-group producing 2048 outputs of a merge at the split points of its
+ * merge path.  Few, long segments are sorted by radix passes over the whole
+ * array instead.  Errors: MICONV_ERR_NULL, MICONV_ERR_SHAPE (n < 1, segments < 1),
  * MICONV_ERR_TOO_LARGE (n >= 2^31 or segments >= 2^21 - 1),
  * MICONV_ERR_WORKSPACE. */
 long vision_argsort_workspace_bytes(long n, int segments);

@@ -5,7 +5,7 @@
 // The paper's designs target integrated GPUs; what carries over to gfx950 is
 // the structure: the scan's register blocking with a Hillis-Steele scan of
 // block totals, the sort's equal-block local sorts followed by cooperative
-// merges that only move segments spanning a merge interface, and NMS's
+// merges that only move segments spanning blocks, and NMS's
 // mapping of the innermost loop onto threads with the output set invalid as a
 // whole first.  On a 64-wide wavefront the Hillis-Steele passes are lane
 // shuffles, the merge path of a work-group is found by a 64-way search (one
@@ -16,7 +16,6 @@
 #include "../../include/miconv.h"
 #include "../../include/mivision.h"
 
-#include <climits>
 
 namespace miconv {
 namespace {
@@ -274,8 +273,7 @@ hipError_t launch_scan(const Src &src, int rows, long n, int32_t *y, bool exclus
 
 constexpr int kSortThreads = 256;
 constexpr int kSortItems = 8;
-constexpr int kSortTile = kSortThreads * kSortItems;   // 2048: block size and merge output per work-group
-constexpr uint64_t kPadKey = ~0ull;                    // sorts after every element of every segment
+constexpr int kSortTile = kSortThreads * kSortItems;   // 2048: merge output per work-group
 
 // Order-preserving image of an fp32 key: ascending (or, descending != 0,
 // descending) float order becomes ascending unsigned order; -0 maps with +0,
@@ -309,21 +307,6 @@ __device__ int find_segment(const int32_t *off, int S, long n, long i)
     return lo;
 }
 
-// Elements are ordered by (composite key, position): all distinct.
-__device__ __forceinline__ bool elem_less(uint64_t ka, int va, uint64_t kb, int vb)
-{
-    return ka < kb || (ka == kb && va < vb);
-}
-
-// The answer for one sorted element: its position local to its segment, or
-// -1 past the last segment.
-__device__ __forceinline__ int32_t local_index(uint64_t k, int v, const int32_t *off, long n)
-{
-    if (k == kPadKey) return -1;
-    const int s = (int)(k >> 32);
-    return (int32_t)(v - seg_at(off, s, n));
-}
-
 // The same search by a whole wavefront for a uniform i: 64 probes per round,
 // so a table of S offsets costs about log64(S) dependent round trips.
 __device__ int find_segment_wave(const int32_t *off, int S, long n, long i)
@@ -349,185 +332,268 @@ __device__ int find_segment_wave(const int32_t *off, int S, long n, long i)
     return lo;
 }
 
-__device__ __forceinline__ uint64_t shfl_xor64(uint64_t v, int d)
+// The lanes of the wavefront whose 8-bit digit equals this lane's, as two
+// 32-bit halves: one ballot per bit.
+__device__ __forceinline__ uint64_t match_digit(uint32_t d)
 {
-    const int lo = __shfl_xor((int)(uint32_t)v, d), hi = __shfl_xor((int)(uint32_t)(v >> 32), d);
-    return ((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo;
+    uint32_t lo = ~0u, hi = ~0u;
+#pragma unroll
+    for (int b = 0; b < 8; ++b) {
+        uint32_t m = (uint32_t)__builtin_amdgcn_sbfe((int)d, b, 1);   // all ones where the bit is set
+        asm("" : "+v"(m));                                            // (the comparison reads m, not d again)
+        const uint64_t bal = __ballot(m != 0);
+        lo &= ~((uint32_t)bal ^ m);
+        hi &= ~((uint32_t)(bal >> 32) ^ m);
+    }
+    return ((uint64_t)hi << 32) | lo;
 }
 
-// One step of the bitonic network between elements J apart (J < 8) held by
-// one thread (elements 8t .. 8t+7 in x): the pair is put in ascending order
-// where bit k of its index is clear, descending where it is set.
-template <int J>
-__device__ __forceinline__ void bitonic_regs(uint64_t (&x)[kSortItems], int t, int k)
+__device__ __forceinline__ int lanes_before(uint64_t set)
 {
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(set >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)set, 0));
+}
+
+// Equal blocks sorted locally: one work-group sorts a block of consecutive
+// positions in LDS by (segment, key, position), as stable radix passes over
+// 8-bit digits, least significant first: four over the key bits and then, if
+// the block holds more than one segment, one or two over the segments.  A
+// pass ranks every element within its wavefront (each holds 64 * ITEMS
+// consecutive elements, lane l of round r element 64 r + l): lanes with the
+// same digit are matched by ballots, earlier rounds counted per wavefront and
+// digit.  Bound by the ballots' VALU work, 5 instructions per bit and round,
+// and in a single block by the passes' chains of barriers (7 us a pass):
+// 2^22 elements take 68 us, one block of 2048 elements 9 us (a bitonic network
+// in 64-bit words: 90 and 21 us).  Lanes finding each other through a table in LDS (an atomic or, a
+// read and a write per round instead of 50 VALU instructions): 84 and 40 us.
+//   Segments that lie within the block are finished: their answers go to out.
+// The elements of the one that began before the block (`head`) and of the
+// one that goes on after it (`tail`) leave as (key bits, position) for the
+// merge passes, with both segments' extents in ext[block].
+constexpr int kTileThreads = 512;
+constexpr int kTileWaves = kTileThreads / 64;
+
+struct TileArgs {
+    const float *keys;
+    const int32_t *off;
+    int S;
+    long n;
+    int descending;
+    uint32_t *K;      // key bits and positions of elements of unfinished segments
+    int32_t *V;
+    int4 *ext;        // per block: [start, end) of its head and tail segments (empty: none)
+    int32_t *out;
+};
+
+// ITEMS per thread: blocks of 8192 positions (16; 70 KB of LDS, two
+// work-groups per CU), 4096 or 2048.
+template <int ITEMS>
+__global__ __launch_bounds__(kTileThreads, 4) void segsort_tile_kernel(TileArgs a)
+{
+    constexpr int BLOCK = kTileThreads * ITEMS;
+    __shared__ uint32_t sk[BLOCK];
+    __shared__ uint16_t sv[BLOCK];
+    __shared__ uint16_t first[BLOCK];    // first position in the block of its q-th segment
+    __shared__ uint16_t cnt[kTileWaves][256];
+    __shared__ int wsum[kTileWaves];
+    __shared__ int s_lo, s_num, s_head, s_tail;
+    const int t = threadIdx.x, lane = t & 63, wid = t >> 6;
+    const long base = (long)blockIdx.x * BLOCK;
+    const long end = seg_at(a.off, a.S, a.n);          // positions from here on belong to no segment
+    const long lim = base + BLOCK < end ? base + BLOCK : end;
+    const int w0 = wid * 64 * ITEMS + lane;
+    uint32_t k[ITEMS];
+    int v[ITEMS];
 #pragma unroll
-    for (int r = 0; r < kSortItems; ++r) {
-        if ((r & J) == 0) {
-            const bool up = ((kSortItems * t + r) & k) == 0;
-            const uint64_t p = x[r], q = x[r + J];
-            if ((p > q) == up) {
-                x[r] = q;
-                x[r + J] = p;
+    for (int r = 0; r < ITEMS; ++r) {
+        v[r] = w0 + 64 * r;
+        const long g = base + v[r];
+        k[r] = g < end ? key_bits(a.keys[g], a.descending) : 0xffffffffu;
+    }
+    if (wid == 0) {
+        int lo = 0, num = 0;
+        long h0 = base, h1 = base, t0 = lim, t1 = lim;
+        if (base < lim) {
+            lo = find_segment_wave(a.off, a.S, a.n, base);
+            const int hi = find_segment_wave(a.off, a.S, a.n, lim - 1);
+            num = hi - lo + 1;
+            const long s0 = seg_at(a.off, lo, a.n), s1 = seg_at(a.off, hi, a.n);
+            const long e0 = seg_at(a.off, lo + 1, a.n), e1 = seg_at(a.off, hi + 1, a.n);
+            if (s0 < base || (num == 1 && e0 > lim)) {
+                h0 = s0;
+                h1 = e0;
+            }
+            if (num > 1 && e1 > lim) {
+                t0 = s1;
+                t1 = e1;
             }
         }
-    }
-}
-
-// Equal blocks sorted locally: block b of the flattened array (kSortTile
-// positions) is sorted by a bitonic network over one 64-bit word per element,
-// (segment: 21 bits | key bits: 32 | position in the block: 11), which orders
-// by segment, key, position and is unique; positions past the last segment
-// get segment 2^21 - 1 and all-ones key bits, so they sort last.  Segments
-// stay in order, each segment's part of the block is sorted.
-//   Thread t holds elements 8t .. 8t+7 in registers: network steps between
-// elements less than 8 apart stay in registers, steps up to 511 apart are
-// lane shuffles within the wavefront, and only the three steps of 512 and
-// 1024 go through LDS.  The segments overlapping the block are found once
-// (two wavefront searches) and their offsets staged in LDS, where each
-// element looks up its own.  The result leaves as (segment << 32 | key bits,
-// position) for the merge passes, or, with a single block, as the answers.
-constexpr uint64_t kPackPadSeg = 0x1FFFFFull;
-
-__global__ __launch_bounds__(kSortThreads) void segsort_block_kernel(const float *keys, const int32_t *off, int S,
-                                                                     long n, int descending, uint64_t *K, int32_t *V,
-                                                                     int32_t *out)
-{
-    __shared__ uint64_t sk[kSortTile];
-    __shared__ long soff[kSortTile + 1];
-    __shared__ int seg_lo, seg_cnt;
-    const int t = threadIdx.x, lane = t & 63, wid = t >> 6;
-    const long base = (long)blockIdx.x * kSortTile;
-    const long end = seg_at(off, S, n);   // positions >= end belong to no segment
-    const long last = (base + kSortTile < end ? base + kSortTile : end) - 1;
-    if (wid == 0 && base <= last) {
-        const int lo = find_segment_wave(off, S, n, base);
-        const int hi = find_segment_wave(off, S, n, last);
-        const int cnt = hi - lo + 1;
         if (lane == 0) {
-            seg_lo = lo;
-            seg_cnt = cnt;
+            s_lo = lo;
+            s_num = num;
+            // slots [0, s_head) and [s_tail, ..) are the head's and the tail's
+            const long hh = h1 > h0 ? h1 : base;
+            s_head = (int)((hh < lim ? hh : lim) - base);
+            const long tt = t1 > t0 ? t0 : lim;
+            s_tail = (int)((tt > base ? tt : base) - base);
+            if (a.ext) a.ext[blockIdx.x] = make_int4((int)h0, (int)h1, (int)t0, (int)t1);
         }
-        if (cnt <= kSortTile)
-            for (int q = lane; q < cnt; q += 64) soff[q] = seg_at(off, lo + q, n);
+        if (num > 1 && num <= BLOCK)
+            for (int q = lane; q < num; q += 64) {
+                const long f = seg_at(a.off, lo + q, a.n) - base;
+                first[q] = (uint16_t)(f < 0 ? 0 : (f < BLOCK ? f : BLOCK - 1));
+            }
     }
+
     __syncthreads();
-    uint64_t x[kSortItems];
+    const int num = s_num, lo = s_lo;
+    int bits = 0;                            // of a segment's order among the block's
+    if (num > BLOCK) bits = 13;
+    else while ((1 << bits) < num) ++bits;
+    const int passes = 4 + (bits + 7) / 8;
+    // One copy of the pass's code: a block runs it from a cold instruction cache.
+#pragma clang loop unroll(disable)
+    for (int p = 0; p < passes; ++p) {
+        const int shift = p < 4 ? 8 * p : 8 * (p - 4);
+        if (p == 4) {
+            // the words become (segment's first position in the block << 16 | its order)
 #pragma unroll
-    for (int r = 0; r < kSortItems; ++r) {
-        const int e = kSortItems * t + r;
-        const long g = base + e;
-        x[r] = (kPackPadSeg << 43) | (0xFFFFFFFFull << 11) | (uint64_t)e;
-        if (g < end) {
-            int sg;
-            if (seg_cnt <= kSortTile) {      // last q with soff[q] <= g
-                int lo = 0, hi = seg_cnt - 1;
-                while (lo < hi) {
-                    const int mid = (lo + hi + 1) >> 1;
-                    if (soff[mid] <= g) lo = mid;
-                    else hi = mid - 1;
+            for (int r = 0; r < ITEMS; ++r) k[r] = 0;
+            if (num <= BLOCK) {
+                for (int len = num; len > 1;) {         // the last q with first[q] <= v, side by side
+                    const int half = len >> 1;
+#pragma unroll
+                    for (int r = 0; r < ITEMS; ++r)
+                        if (first[k[r] + half] <= v[r]) k[r] += half;
+                    len -= half;
                 }
-                sg = seg_lo + lo;
+#pragma unroll
+                for (int r = 0; r < ITEMS; ++r) k[r] |= (uint32_t)first[k[r]] << 16;
             } else {
-                sg = find_segment(off, S, n, g);
-            }
-            x[r] = ((uint64_t)sg << 43) | ((uint64_t)key_bits(keys[g], descending) << 11) | (uint64_t)e;
-        }
-    }
-    for (int k = 2; k <= kSortTile; k <<= 1) {
-        for (int j = k >> 1; j >= kSortItems; j >>= 1) {
-            // partner of element e = 8t + r is e ^ j = 8(t ^ (j/8)) + r
-            const bool up = ((kSortItems * t) & k) == 0;
-            const bool lower = ((kSortItems * t) & j) == 0;
-            uint64_t y[kSortItems];
-            if (j < 64 * kSortItems) {
-#pragma unroll
-                for (int r = 0; r < kSortItems; ++r) y[r] = shfl_xor64(x[r], j / kSortItems);
-            } else {
-                __syncthreads();   // everyone is done reading the previous LDS step
-#pragma unroll
-                for (int r = 0; r < kSortItems; ++r) sk[kSortItems * t + r] = x[r];
-                __syncthreads();
-#pragma unroll
-                for (int r = 0; r < kSortItems; ++r) y[r] = sk[(kSortItems * t + r) ^ j];
-            }
-#pragma unroll
-            for (int r = 0; r < kSortItems; ++r) {
-                const bool keep_min = lower == up;
-                const uint64_t mn = x[r] < y[r] ? x[r] : y[r], mx = x[r] < y[r] ? y[r] : x[r];
-                x[r] = keep_min ? mn : mx;
+                // more segments than positions (most of them empty): a
+                // segment's first position stands for its order
+                for (int r = 0; r < ITEMS; ++r) {
+                    const long g = base + v[r] < lim ? base + v[r] : lim - 1;
+                    const long f = seg_at(a.off, find_segment(a.off, a.S, a.n, g), a.n) - base;
+                    k[r] = (uint32_t)(f < 0 ? 0 : f) * 0x10001u;
+                }
             }
         }
-        // steps between a thread's own elements
-        if (k > 4) bitonic_regs<4>(x, t, k);
-        if (k > 2) bitonic_regs<2>(x, t, k);
-        bitonic_regs<1>(x, t, k);
-    }
+        for (int i = t; i < kTileWaves * 128; i += kTileThreads) reinterpret_cast<uint32_t *>(&cnt[0][0])[i] = 0;
+        __syncthreads();
+        int rank[ITEMS];
 #pragma unroll
-    for (int r = 0; r < kSortItems; ++r) {
-        const long g = base + kSortItems * t + r;
-        if (g >= n) continue;
-        const uint64_t w = x[r];
-        const bool pad = (w >> 43) == kPackPadSeg;
-        const uint64_t key = pad ? kPadKey : ((w >> 43) << 32) | ((w >> 11) & 0xFFFFFFFFull);
-        const int32_t v = (int32_t)(base + (long)(w & 0x7FF));
-        if (out) out[g] = local_index(key, v, off, n);
-        else {
-            K[g] = key;
-            V[g] = v;
+        for (int r = 0; r < ITEMS; ++r) {
+            const uint32_t d = (k[r] >> shift) & 255;
+            const uint64_t same = match_digit(d);
+            const int before = lanes_before(same);
+            const int c = cnt[wid][d];
+            rank[r] = c + before;
+            if (before == 0) cnt[wid][d] = (uint16_t)(c + __popcll(same));
+        }
+        __syncthreads();
+        int mine = 0, total;
+        if (t < 256)
+#pragma unroll
+            for (int w = 0; w < kTileWaves; ++w) mine += cnt[w][t];
+        int at = wg_scan_incl<kTileThreads>(mine, wsum, &total) - mine;
+        if (t < 256) {
+#pragma unroll
+            for (int w = 0; w < kTileWaves; ++w) {
+                const int c = cnt[w][t];
+                cnt[w][t] = (uint16_t)at;
+                at += c;
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < ITEMS; ++r) {
+            const int slot = cnt[wid][(k[r] >> shift) & 255] + rank[r];
+            sk[slot] = k[r];
+            sv[slot] = (uint16_t)v[r];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < ITEMS; ++r) {
+            k[r] = sk[w0 + 64 * r];
+            v[r] = sv[w0 + 64 * r];
+        }
+    }
+    // the words are key bits if the block holds one segment
+    const long s0 = num == 1 ? seg_at(a.off, lo, a.n) : 0;
+#pragma unroll
+    for (int r = 0; r < ITEMS; ++r) {
+        const int slot = w0 + 64 * r;
+        const long g = base + slot;
+        if (g >= a.n) break;
+        const long pos = base + v[r];
+        if (g >= end) {
+            a.out[g] = -1;
+        } else if (slot < s_head || slot >= s_tail) {
+            a.K[g] = num == 1 ? k[r] : key_bits(a.keys[pos], a.descending);
+            a.V[g] = (int32_t)pos;
+        } else {
+            a.out[g] = num == 1 ? (int32_t)(pos - s0) : v[r] - (int32_t)(k[r] >> 16);
         }
     }
 }
 
-// One merge pass: runs of length L (sorted) merged pairwise into runs of 2L.
-// Work-group w writes outputs [w*C, w*C + C) (C = kSortTile) of the pair
-// containing them.  Where that pair's two runs meet at a segment boundary
-// (the last element of A in an earlier segment than the first of B) the pair
-// is already in order and the chunk is copied: only segments that span the
-// interface between two runs are reordered.  Otherwise the first two
-// wavefronts find where diagonals d0 and d1 of the merge path cross (how many
-// of the first d outputs come from A), each by a 64-way search (64 probes
-// per round), the work-group stages the A and B elements between the two
-// crossings in LDS, every thread finds its own crossing there by bisection
-// and merges kSortItems outputs sequentially.  The last pass writes the
-// answers (out) instead of keys.
-__global__ __launch_bounds__(kSortThreads) void segsort_merge_kernel(const uint64_t *Ki, const int32_t *Vi,
-                                                                     uint64_t *Ko, int32_t *Vo, long n, long L,
-                                                                     const int32_t *off, int32_t *out)
+// One merge pass over the segments that span blocks.  A segment's part in
+// each of its blocks is a sorted run; pass j merges its runs of 2^j blocks,
+// counted from the segment's first block, pairwise, so a segment over m blocks
+// is finished after ceil(log2 m) passes wherever it lies, and segments that
+// are finished are not touched: a pass moves only what is still unsorted.
+// 2^22 keys in 4096 segments take 26 us in all nine passes (the first two 20;
+// passes with nothing to do 2 to 4 us), where moving every element in every
+// pass took 40 us a pass.
+// Work-group (w, y) writes outputs [w*C, w*C + C) (C = kSortTile) as far as
+// they belong to the head (y = 0) or tail (1) segment of its block: the first
+// two wavefronts find where the chunk's ends cross the merge path (64 probes
+// per round), the elements between are staged in LDS, every thread finds its
+// own crossing by bisection and merges kSortItems outputs.  Equal keys: the
+// first run's come first (its positions are lower).  The pass that completes
+// a segment writes its answers.
+struct MergeArgs {
+    const uint32_t *Ki;
+    const int32_t *Vi;
+    uint32_t *Ko;
+    int32_t *Vo;
+    const int4 *ext;
+    int32_t *out;
+    long n;
+    int log_block;    // positions per block: 2^log_block
+    int log_run;      // the pass's runs: 2^log_run blocks
+};
+
+__global__ __launch_bounds__(kSortThreads) void segsort_merge_kernel(MergeArgs a)
 {
-    constexpr int C = kSortTile;
-    __shared__ uint64_t sk[C];
-    __shared__ int32_t sv[C];
+    __shared__ uint32_t sk[kSortTile];
+    __shared__ int32_t sv[kSortTile];
     __shared__ long split[2];
+    const long w0 = (long)blockIdx.x * kSortTile;
+    const int4 e = a.ext[w0 >> a.log_block];
+    const long sa = blockIdx.y ? e.z : e.x, sb = blockIdx.y ? e.w : e.y;   // the segment
+    if (sb <= sa) return;
+    const long ta = sa >> a.log_block;                                        // its first block
+    const long runs = (((sb - 1) >> a.log_block) - ta) >> a.log_run;            // runs of this pass, less one
+    if (runs == 0) return;                                                 // finished before
+    const long c0 = sa > w0 ? sa : w0;
+    const long w1 = w0 + kSortTile < a.n ? w0 + kSortTile : a.n;
+    const long c1 = sb < w1 ? sb : w1;
+    if (c1 <= c0) return;
     const int t = threadIdx.x, lane = t & 63, wid = t >> 6;
-    const long o0 = (long)blockIdx.x * C;
-    const long p0 = o0 / (2 * L) * (2 * L);
-    const long na = n - p0 < L ? n - p0 : L;
-    const long nbr = n - p0 - L;
-    const long nb = nbr <= 0 ? 0 : (nbr < L ? nbr : L);
-    const long d0 = o0 - p0;
-    const long d1 = d0 + C < na + nb ? d0 + C : na + nb;
-    const int cnt = (int)(d1 - d0);
-    const uint64_t *KA = Ki + p0, *KB = Ki + p0 + L;
-    const int32_t *VA = Vi + p0, *VB = Vi + p0 + L;
-
-    // already in order: no B, or A's last element precedes B's first (in
-    // particular when A ends in an earlier segment than B starts)
-    const bool concat = nb == 0 || elem_less(KA[na - 1], VA[na - 1], KB[0], VB[0]);
-    if (concat) {
-        for (int i = t; i < cnt; i += kSortThreads) {
-            const long g = o0 + i;
-            const uint64_t k = Ki[g];
-            const int32_t v = Vi[g];
-            if (out) out[g] = local_index(k, v, off, n);
-            else {
-                Ko[g] = k;
-                Vo[g] = v;
-            }
-        }
-        return;
-    }
-
+    const long pair = ((w0 >> a.log_block) - ta) >> (a.log_run + 1);
+    const long p0 = (ta + (pair << (a.log_run + 1))) << a.log_block;
+    const long L = 1L << (a.log_block + a.log_run);
+    const long pm = p0 + L, p1 = pm + L;
+    const long A0 = sa > p0 ? sa : p0, A1 = sb < pm ? sb : pm;             // the first run
+    const long B0 = pm, B1 = sb < p1 ? sb : p1;                            // the second
+    const long na = A1 - A0, nb = B1 > B0 ? B1 - B0 : 0;
+    const long base = A0;
+    const bool last = runs == 1;
+    const uint32_t *KA = a.Ki + A0, *KB = a.Ki + B0;
+    const int32_t *VA = a.Vi + A0, *VB = a.Vi + B0;
+    const long d0 = c0 - base, d1 = c1 - base;
+    const int cnt = (int)(c1 - c0);
     if (wid < 2) {
         const long d = wid ? d1 : d0;
         long lo = d - nb > 0 ? d - nb : 0, hi = d < na ? d : na;
@@ -538,7 +604,7 @@ __global__ __launch_bounds__(kSortThreads) void segsort_merge_kernel(const uint6
             const long step = (span + 63) / 64;
             const long m = lo + (long)lane * step;
             bool f = false;
-            if (m < hi) f = elem_less(KB[d - 1 - m], VB[d - 1 - m], KA[m], VA[m]);
+            if (m < hi) f = KB[d - 1 - m] < KA[m];
             const uint64_t bal = __ballot(f);
             if (bal) {
                 const int l = __ffsll((unsigned long long)bal) - 1;
@@ -546,8 +612,8 @@ __global__ __launch_bounds__(kSortThreads) void segsort_merge_kernel(const uint6
                 lo = l ? lo + (long)(l - 1) * step + 1 : lo;
                 hi = ml;
             } else {
-                const long last = (span - 1) / step < 63 ? (span - 1) / step : 63;
-                lo = lo + last * step + 1;
+                const long past = (span - 1) / step < 63 ? (span - 1) / step : 63;
+                lo = lo + past * step + 1;
             }
         }
         if (lane == 0) split[wid] = lo;
@@ -557,13 +623,8 @@ __global__ __launch_bounds__(kSortThreads) void segsort_merge_kernel(const uint6
     const int ca = (int)(a1 - a0 < cnt ? a1 - a0 : cnt);   // crossings are monotone: 0 <= ca <= cnt
     const long b0 = d0 - a0;
     for (int i = t; i < cnt; i += kSortThreads) {
-        if (i < ca) {
-            sk[i] = KA[a0 + i];
-            sv[i] = VA[a0 + i];
-        } else {
-            sk[i] = KB[b0 + (i - ca)];
-            sv[i] = VB[b0 + (i - ca)];
-        }
+        sk[i] = i < ca ? KA[a0 + i] : KB[b0 + (i - ca)];
+        sv[i] = i < ca ? VA[a0 + i] : VB[b0 + (i - ca)];
     }
     __syncthreads();
     const int cb = cnt - ca;
@@ -571,18 +632,18 @@ __global__ __launch_bounds__(kSortThreads) void segsort_merge_kernel(const uint6
     int lo = dt - cb > 0 ? dt - cb : 0, hi = dt < ca ? dt : ca;
     while (lo < hi) {
         const int mid = (lo + hi) >> 1;
-        if (elem_less(sk[ca + dt - 1 - mid], sv[ca + dt - 1 - mid], sk[mid], sv[mid])) hi = mid;
+        if (sk[ca + dt - 1 - mid] < sk[mid]) hi = mid;
         else lo = mid + 1;
     }
     int ia = lo, ib = dt - lo;
-    uint64_t rk[kSortItems];
+    uint32_t rk[kSortItems];
     int32_t rv[kSortItems];
 #pragma unroll
     for (int k = 0; k < kSortItems; ++k) {
-        rk[k] = kPadKey;
-        rv[k] = INT_MAX;
+        rk[k] = 0;
+        rv[k] = 0;
         if (dt + k >= cnt) continue;
-        const bool take_a = ib >= cb || (ia < ca && elem_less(sk[ia], sv[ia], sk[ca + ib], sv[ca + ib]));
+        const bool take_a = ib >= cb || (ia < ca && sk[ia] <= sk[ca + ib]);
         const int src = take_a ? ia++ : ca + ib++;
         rk[k] = sk[src];
         rv[k] = sv[src];
@@ -596,11 +657,185 @@ __global__ __launch_bounds__(kSortThreads) void segsort_merge_kernel(const uint6
         }
     __syncthreads();
     for (int i = t; i < cnt; i += kSortThreads) {
-        const long g = o0 + i;
-        if (out) out[g] = local_index(sk[i], sv[i], off, n);
+        if (last) a.out[c0 + i] = (int32_t)(sv[i] - sa);
         else {
-            Ko[g] = sk[i];
-            Vo[g] = sv[i];
+            a.Ko[c0 + i] = sk[i];
+            a.Vo[c0 + i] = sv[i];
+        }
+    }
+}
+
+// Long segments: least-significant-digit radix passes over the whole array,
+// four over the key bits and, with more than one segment (at most 256), one
+// over the segment.  Each reads and writes 8 bytes per element once, whatever
+// the segments' lengths, where the merge passes move every element of a
+// segment log2(its blocks) times.  A pass is three launches: digit counts of
+// every tile (radix_count_kernel), their exclusive scan digit by digit
+// (scan_rows_kernel, one row of tile counts per digit), and the scatter
+// (radix_scatter_kernel, 20 us for 2^22 elements, VALU-bound by the ballots as
+// the block sort is).  Every step is stable.
+constexpr int kRadixThreads = 512;
+constexpr int kRadixItems = 16;
+constexpr int kRadixTile = kRadixThreads * kRadixItems;   // 8192: two work-groups per CU in the scatter
+constexpr int kRadixBins = 256;
+constexpr int kRadixWaves = kRadixThreads / 64;
+
+struct RadixArgs {
+    const float *keys;        // first pass: the keys as given, positions implied
+    const uint32_t *Ki;       // other passes: key bits, or segments in the segment passes
+    const int32_t *Vi;        // positions
+    uint32_t *Ko;
+    int32_t *Vo;
+    int32_t *out;             // last pass: the answers
+    const int32_t *off;
+    int32_t *counts;          // [256][tiles]
+    const int32_t *totals;    // [256]
+    long n;
+    int S, tiles, descending;
+    int shift;                // the digit: 8 bits from here
+    int to_segment;           // write the element's segment in place of its key
+};
+
+// Key bits of element i of the first pass: positions past the segments sort
+// after everything (NaNs, which share their bits, come earlier in the array).
+__device__ __forceinline__ uint32_t radix_key(const RadixArgs &a, long i, long end)
+{
+    return a.keys ? (i < end ? key_bits(a.keys[i], a.descending) : 0xffffffffu) : a.Ki[i];
+}
+
+__global__ __launch_bounds__(kRadixThreads) void radix_count_kernel(RadixArgs a)
+{
+    __shared__ int cnt[kRadixWaves][kRadixBins];
+    const int t = threadIdx.x, wid = t >> 6;
+    for (int i = t; i < kRadixWaves * kRadixBins; i += kRadixThreads) (&cnt[0][0])[i] = 0;
+    const long base = (long)blockIdx.x * kRadixTile;
+    const long end = a.keys ? seg_at(a.off, a.S, a.n) : 0;
+    constexpr uint32_t mask = kRadixBins - 1;
+    uint32_t k[kRadixItems];
+#pragma unroll
+    for (int r = 0; r < kRadixItems; ++r) {
+        const long i = base + r * kRadixThreads + t;
+        k[r] = i < a.n ? radix_key(a, i, end) : 0;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < kRadixItems; ++r)
+        if (base + r * kRadixThreads + t < a.n) atomicAdd(&cnt[wid][(k[r] >> a.shift) & mask], 1);
+    __syncthreads();
+    if (t < kRadixBins) {
+        int s = 0;
+#pragma unroll
+        for (int w = 0; w < kRadixWaves; ++w) s += cnt[w][t];
+        a.counts[(long)t * a.tiles + blockIdx.x] = s;
+    }
+}
+
+// One tile's elements to their places.  Wavefront w holds 1024 consecutive
+// elements, lane l of round r element 64 r + l: the elements of one digit
+// before it in its round are counted by matching the digit's bits across the
+// lanes, those in earlier rounds in a counter per wavefront and digit.  The
+// tile is then gathered digit by digit in LDS, so that the elements of a digit
+// leave as one run.
+__global__ __launch_bounds__(kRadixThreads, 4) void radix_scatter_kernel(RadixArgs a)
+{
+    __shared__ uint32_t skv[2 * kRadixTile];
+    uint32_t *sk = skv;
+    int32_t *sv = reinterpret_cast<int32_t *>(skv) + kRadixTile;
+    __shared__ int cnt[kRadixWaves][kRadixBins];
+    __shared__ int gbase[kRadixBins];
+    __shared__ int wsum[kRadixWaves];
+    const int t = threadIdx.x, lane = t & 63, wid = t >> 6;
+    const long base = (long)blockIdx.x * kRadixTile;
+    const long end = seg_at(a.off, a.S, a.n);
+    const long w0 = base + wid * 64 * kRadixItems;
+    constexpr uint32_t mask = kRadixBins - 1;
+    uint32_t k[kRadixItems];
+    int v[kRadixItems];
+#pragma unroll
+    for (int r = 0; r < kRadixItems; ++r) {
+        const long i = w0 + r * 64 + lane;
+        k[r] = i < a.n ? radix_key(a, i, end) : 0;
+        v[r] = i < a.n ? (a.keys ? (int)i : a.Vi[i]) : 0;
+    }
+    // where the tile's elements of digit t go
+    int place = 0;
+    if (t < kRadixBins) place = a.counts[(long)t * a.tiles + blockIdx.x];
+    int total;
+    {
+        const int tot = t < kRadixBins ? a.totals[t] : 0;
+        place += wg_scan_incl<kRadixThreads>(tot, wsum, &total) - tot;
+    }
+    for (int i = t; i < kRadixWaves * kRadixBins; i += kRadixThreads) (&cnt[0][0])[i] = 0;
+    // segments of the elements' positions: the last with offset <= v, the
+    // searches side by side
+    uint32_t seg[kRadixItems];
+    if (a.to_segment) {
+        if (t < a.S) sv[t] = (int32_t)seg_at(a.off, t, a.n);     // S <= 256
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < kRadixItems; ++r) seg[r] = 0;
+        for (int len = a.S; len > 1;) {
+            const int half = len >> 1;
+#pragma unroll
+            for (int r = 0; r < kRadixItems; ++r)
+                if (sv[seg[r] + half] <= v[r]) seg[r] += half;
+            len -= half;
+        }
+    }
+    __syncthreads();
+    int rank[kRadixItems];
+#pragma unroll
+    for (int r = 0; r < kRadixItems; ++r) {
+        const bool ok = w0 + r * 64 + lane < a.n;
+        const uint32_t d = (k[r] >> a.shift) & mask;
+        const uint64_t same = __ballot(ok) & match_digit(d);
+        const int before = lanes_before(same);
+        const int c = cnt[wid][d];
+        rank[r] = c + before;
+        if (ok && before == 0) cnt[wid][d] = c + __popcll(same);
+    }
+    __syncthreads();
+    // first local slot of every digit, and of every wavefront's share of it
+    int mine = 0;
+    if (t < kRadixBins) {
+#pragma unroll
+        for (int w = 0; w < kRadixWaves; ++w) {
+            const int c = cnt[w][t];
+            cnt[w][t] = mine;
+            mine += c;
+        }
+    }
+    const int start = wg_scan_incl<kRadixThreads>(mine, wsum, &total) - mine;
+    if (t < kRadixBins) {
+        gbase[t] = place - start;
+#pragma unroll
+        for (int w = 0; w < kRadixWaves; ++w) cnt[w][t] += start;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < kRadixItems; ++r) {
+        if (w0 + r * 64 + lane >= a.n) continue;
+        const uint32_t d = (k[r] >> a.shift) & mask;
+        const int slot = cnt[wid][d] + rank[r];
+        // the segment travels with the digit that places it
+        sk[slot] = a.to_segment ? seg[r] | (d << 24) : k[r];
+        sv[slot] = v[r];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kRadixItems; ++i) {
+        const int slot = i * kRadixThreads + t;
+        if (base + slot >= a.n) break;
+        const uint32_t key = sk[slot];
+        const uint32_t d = a.to_segment ? key >> 24 : (key >> a.shift) & mask;
+        const long dst = gbase[d] + slot;
+        const int pos = sv[slot];
+        if (a.out) {
+            const uint32_t s = a.S == 1 ? 0 : key;
+            a.out[dst] = pos < end ? (int32_t)(pos - seg_at(a.off, (int)s, a.n)) : -1;
+        } else {
+            a.Ko[dst] = a.to_segment ? key & 0xffffffu : key;
+            a.Vo[dst] = pos;
         }
     }
 }
@@ -609,31 +844,111 @@ long align256(long b) { return (b + 255) / 256 * 256; }
 
 long argsort_ws_bytes(long n) { return n <= kSortTile ? 0 : 2 * align256(n * 8) + 2 * align256(n * 4); }
 
-// The whole sort: local block sorts, then merge passes L = 2048, 4096, ...
-// ping-ponging between two key/position buffers; the last pass (or the block
-// sort, for one block) writes the answers.
+// Where the radix passes win over block sorts and merges (measured, us: one
+// segment of 500 thousand keys 102 and 101, of 1 million 137 and 110, of 2^22
+// 295 and 147; 2^22 keys in 30 segments 212 and 191, in 100 175 and 193; 2
+// million in 6 157 and 143, in 20 even; 1 million in 10 123 and 140).
+bool radix_pays(long n, int S)
+{
+    return S == 1 ? n >= 500000 : n >= 1500000 && S <= kRadixBins && n / S >= 100000;
+}
+
+hipError_t launch_radix(const float *keys, const int32_t *off, int S, long n, int descending, int32_t *out, void *ws,
+                        hipStream_t st)
+{
+    // 16 n bytes of keys and positions, n/8 of counts: within argsort_ws_bytes
+    char *p = static_cast<char *>(ws);
+    uint32_t *K[2];
+    int32_t *V[2];
+    for (int i = 0; i < 2; ++i) {
+        K[i] = reinterpret_cast<uint32_t *>(p);
+        V[i] = reinterpret_cast<int32_t *>(p + align256(n * 4));
+        p += 2 * align256(n * 4);
+    }
+    RadixArgs a{};
+    a.off = off;
+    a.n = n;
+    a.S = S;
+    a.tiles = (int)((n + kRadixTile - 1) / kRadixTile);
+    a.descending = descending;
+    int32_t *totals = reinterpret_cast<int32_t *>(p);
+    a.totals = totals;
+    a.counts = totals + kRadixBins;
+    const int passes = S > 1 ? 5 : 4;
+    for (int i = 0; i < passes; ++i) {
+        a.keys = i == 0 ? keys : nullptr;
+        a.Ki = K[(i & 1) ^ 1];
+        a.Vi = V[(i & 1) ^ 1];
+        a.Ko = K[i & 1];
+        a.Vo = V[i & 1];
+        a.out = i == passes - 1 ? out : nullptr;
+        a.to_segment = i == 3 && S > 1;
+        a.shift = i < 4 ? 8 * i : 0;
+        launch_kernel(radix_count_kernel, dim3((unsigned)a.tiles), dim3(kRadixThreads), 0, st, a);
+        launch_kernel(scan_rows_kernel<kScanThreads, SrcI32>, dim3(kRadixBins), dim3(kScanThreads), 0, st,
+                      SrcI32{a.counts}, (long)a.tiles, a.counts, 1, totals);
+        launch_kernel(radix_scatter_kernel, dim3((unsigned)a.tiles), dim3(kRadixThreads), 0, st, a);
+    }
+    return hipGetLastError();
+}
+
+// Elements per thread of the block sorts.  Small blocks have the shorter chain
+// of rounds and put more CUs to work, large ones leave fewer merge passes
+// (measured with 4 / 8 / 16, us: 1500 keys in 6 segments 13 / 19 / 34; 4096 in
+// one 19 / 16 / 28; 200 thousand in 300 33 / 39 / 55, in 3 72 / 70 / 78; 1
+// million in 1000 52 / 53 / 62; 2^22 in 4096 124 / 117 / 96).
+int sort_items(long n, int S)
+{
+    if (n > 1500000) return 16;
+    return n > 2048 && (n <= 4096 || n / S >= 8192) ? 8 : 4;
+}
+
+// The whole sort: local block sorts, then, for segments that span blocks,
+// merge passes over runs of 1, 2, 4, ... blocks, ping-ponging between two
+// key/position buffers.
 hipError_t launch_segsort(const float *keys, const int32_t *off, int S, long n, int descending, int32_t *out,
                           void *ws, hipStream_t st)
 {
-    const unsigned blocks = (unsigned)((n + kSortTile - 1) / kSortTile);
-    if (n <= kSortTile) {
-        launch_kernel(segsort_block_kernel, dim3(blocks), dim3(kSortThreads), 0, st, keys, off, S, n, descending,
-                      (uint64_t *)nullptr, (int32_t *)nullptr, out);
+    if (radix_pays(n, S)) return launch_radix(keys, off, S, n, descending, out, ws, st);
+    const int items = sort_items(n, S);
+    const int block = kTileThreads * items;
+    const unsigned blocks = (unsigned)((n + block - 1) / block);
+    TileArgs ta{keys, off, S, n, descending, nullptr, nullptr, nullptr, out};
+    auto launch_blocks = [&] {
+        if (items == 4) launch_kernel(segsort_tile_kernel<4>, dim3(blocks), dim3(kTileThreads), 0, st, ta);
+        else if (items == 8) launch_kernel(segsort_tile_kernel<8>, dim3(blocks), dim3(kTileThreads), 0, st, ta);
+        else launch_kernel(segsort_tile_kernel<16>, dim3(blocks), dim3(kTileThreads), 0, st, ta);
+    };
+    if (blocks == 1) {
+        launch_blocks();
         return hipGetLastError();
     }
     char *p = static_cast<char *>(ws);
-    uint64_t *K[2] = {reinterpret_cast<uint64_t *>(p), reinterpret_cast<uint64_t *>(p + align256(n * 8))};
-    p += 2 * align256(n * 8);
-    int32_t *V[2] = {reinterpret_cast<int32_t *>(p), reinterpret_cast<int32_t *>(p + align256(n * 4))};
-    launch_kernel(segsort_block_kernel, dim3(blocks), dim3(kSortThreads), 0, st, keys, off, S, n, descending, K[0],
-                  V[0], (int32_t *)nullptr);
+    uint32_t *K[2];
+    int32_t *V[2];
+    for (int i = 0; i < 2; ++i) {
+        K[i] = reinterpret_cast<uint32_t *>(p);
+        V[i] = reinterpret_cast<int32_t *>(p + align256(n * 4));
+        p += 2 * align256(n * 4);
+    }
+    ta.K = K[0];
+    ta.V = V[0];
+    ta.ext = reinterpret_cast<int4 *>(p);     // 16 bytes per block: within argsort_ws_bytes
+    launch_blocks();
+    MergeArgs m{};
+    while ((1 << m.log_block) < block) ++m.log_block;
+    m.ext = ta.ext;
+    m.out = out;
+    m.n = n;
     int cur = 0;
-    for (long L = kSortTile; L < n; L *= 2) {
-        const bool last = 2 * L >= n;
-        launch_kernel(segsort_merge_kernel, dim3(blocks), dim3(kSortThreads), 0, st,
-                      static_cast<const uint64_t *>(K[cur]), static_cast<const int32_t *>(V[cur]), K[cur ^ 1],
-                      V[cur ^ 1], n, L, off, last ? out : (int32_t *)nullptr);
-        cur ^= 1;
+    for (int j = 0; (1L << j) < (long)blocks; ++j, cur ^= 1) {
+        m.Ki = K[cur];
+        m.Vi = V[cur];
+        m.Ko = K[cur ^ 1];
+        m.Vo = V[cur ^ 1];
+        m.log_run = j;
+        launch_kernel(segsort_merge_kernel, dim3((unsigned)((n + kSortTile - 1) / kSortTile), 2), dim3(kSortThreads),
+                      0, st, m);
     }
     return hipGetLastError();
 }

@@ -119,6 +119,32 @@ def test_argsort_positions_past_the_segments():
     assert sorted(out[:1000].tolist()) == list(range(1000))
 
 
+# Edges of the blocks (2048, 4096 or 8192 elements by size and segments) and of
+# the merge passes over them, more segments than a block has positions (most
+# of them empty), and the radix passes over few long segments (n >= 500000 for
+# one, 1.5 million for more).
+ARGSORT_BLOCK_CASES = [   # (n, segments, ties)
+    (2047, 1, False), (2048, 5, True), (4096, 1, False), (4097, 2, True), (8192, 8, True), (8193, 1, False),
+    (16384, 2, True), (16385, 16385, False), (24577, 3, False), (70000, 1, True), (12000, 40000, False),
+    (499999, 1, False), (500000, 1, True), (507904, 1, False), (1500000, 15, True), (1500001, 3, False),
+    (1500001, 20, True), (1600000, 900, False),
+]
+
+
+@pytest.mark.parametrize("n,segments,ties", ARGSORT_BLOCK_CASES, ids=[f"{a}-{b}-{c}" for a, b, c in ARGSORT_BLOCK_CASES])
+def test_argsort_blocks_and_radix_bitwise(oracle_lib, n, segments, ties):
+    keys = det.keys(n, seed=n + segments, ties=ties)
+    keys[::97], keys[5::101], keys[7::103] = np.nan, -0.0, np.inf
+    off = det.segment_offsets(segments, n, seed=segments)
+    for descending in (True, False):
+        _check_argsort(oracle_lib, keys, off, descending)
+    # the last 300 positions belong to no segment
+    cut = np.minimum(off, n - 300).astype(np.int32)
+    out = vision.segmented_argsort(dev(keys), dev(cut)).cpu().numpy()
+    np.testing.assert_array_equal(out[:n - 300], oracle_lib.segmented_argsort(keys[:n - 300], cut, True))
+    assert np.all(out[n - 300:] == -1)
+
+
 # ---------------------------------------------------------------- box_nms
 
 def _check_nms(oracle_lib, data, **kw):
