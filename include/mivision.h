@@ -86,10 +86,10 @@ int vision_segmented_argsort(long n, int segments, const float *keys, const int3
  * each operation rounded, no fused multiply-add; 0 when the union is 0).
  * Kept rows are copied to out[b][0 ..], in rank order; every other value of
  * out is -1 (the output is first set invalid as a whole, Sec. 4.3).
- * Pipeline: a fill kernel sets out to -1; a three-stage scan of the
- * candidate flags gives each candidate its slot; the candidates' scores are
- * compacted per image and ranked by segmented argsort; a kernel grid over
- * (candidate block, candidate block, image) computes which later candidate
+ * Pipeline: one pass over the rows sets out to -1 and collects the
+ * candidates, chunk by chunk; one work-group per image picks the topk best
+ * (radix select) and ranks them; a kernel grid over (candidate block,
+ * candidate block, image) computes which later candidate
  * each candidate suppresses as 64-bit masks (the innermost loop on threads,
  * the loop above it on work-groups, images on the grid); one wavefront per
  * image then walks the candidates in rank order, OR-ing the mask rows of

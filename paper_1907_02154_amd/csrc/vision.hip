@@ -64,24 +64,12 @@ __device__ int wg_scan_incl(int v, int *wsum, int *total)
     return r;
 }
 
-// Sources of scanned values: an int32 array, or the candidate flag of a
-// detection row (score > threshold).
-// SrcI32 can also be read four values per 16-byte load where aligned.
+// The scanned values: an int32 array, four values per 16-byte load where aligned.
 struct SrcI32 {
-    static constexpr bool kVec = true;
     const int32_t *x;
     __device__ int operator()(long i) const { return x[i]; }
     __device__ bool aligned(long i) const { return (((uintptr_t)(x + i)) & 15) == 0; }
     __device__ int4 vec(long i) const { return *reinterpret_cast<const int4 *>(x + i); }
-};
-struct SrcScore {
-    static constexpr bool kVec = false;
-    const float *data;
-    int width, score_index;
-    float thresh;
-    __device__ int operator()(long i) const { return data[i * width + score_index] > thresh ? 1 : 0; }
-    __device__ bool aligned(long) const { return false; }
-    __device__ int4 vec(long) const { return int4{}; }
 };
 
 // The three stages on one tile [base, base + len) (len <= NT * kScanItems),
@@ -96,7 +84,7 @@ __device__ int scan_tile(const Src &src, long base, int len, int32_t *y, int car
                          int *wsum)
 {
     const int t = threadIdx.x;
-    if (Src::kVec && len == NT * kScanItems && src.aligned(base)) {
+    if (len == NT * kScanItems && src.aligned(base)) {
         // whole aligned tile: 16-byte loads, four values each (a group of
         // four never straddles a pad word)
 #pragma unroll
@@ -184,7 +172,7 @@ __global__ __launch_bounds__(kScanThreads) void scan_upsweep_kernel(Src src, lon
     const long rem = n - (long)blockIdx.x * kScanTile;
     const int len = (int)(rem < kScanTile ? rem : kScanTile);
     int s = 0;
-    if (Src::kVec && len == kScanTile && src.aligned(base)) {
+    if (len == kScanTile && src.aligned(base)) {
 #pragma unroll
         for (int j = 0; j < kScanItems / 4; ++j) {
             const int4 q = src.vec(base + 4L * (j * kScanThreads + threadIdx.x));
@@ -353,6 +341,58 @@ __device__ __forceinline__ int lanes_before(uint64_t set)
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(set >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)set, 0));
 }
 
+// One stable radix pass in LDS over the digit (x >> shift) & 255 of THREADS *
+// ITEMS words, each with a 16-bit index v: wavefront w holds 64 * ITEMS
+// consecutive ones, lane l of round r word 64 r + l.  On return x and v hold
+// the words in their new order.
+template <int THREADS, int ITEMS>
+__device__ __forceinline__ void lds_radix_pass(uint32_t (&x)[ITEMS], int (&v)[ITEMS], int shift, uint32_t *sk,
+                                               uint16_t *sv, uint16_t (*cnt)[256], int *wsum)
+{
+    constexpr int WAVES = THREADS / 64;
+    const int t = threadIdx.x, lane = t & 63, wid = t >> 6;
+    const int w0 = wid * 64 * ITEMS + lane;
+    for (int i = t; i < WAVES * 128; i += THREADS) reinterpret_cast<uint32_t *>(&cnt[0][0])[i] = 0;
+    __syncthreads();
+    int rank[ITEMS];
+#pragma unroll
+    for (int r = 0; r < ITEMS; ++r) {
+        const uint32_t d = (x[r] >> shift) & 255;
+        const uint64_t same = match_digit(d);
+        const int before = lanes_before(same);
+        const int c = cnt[wid][d];
+        rank[r] = c + before;
+        if (before == 0) cnt[wid][d] = (uint16_t)(c + __popcll(same));
+    }
+    __syncthreads();
+    int mine = 0, total;
+    if (t < 256)
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w) mine += cnt[w][t];
+    int at = wg_scan_incl<THREADS>(mine, wsum, &total) - mine;
+    if (t < 256) {
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w) {
+            const int c = cnt[w][t];
+            cnt[w][t] = (uint16_t)at;
+            at += c;
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < ITEMS; ++r) {
+        const int slot = cnt[wid][(x[r] >> shift) & 255] + rank[r];
+        sk[slot] = x[r];
+        sv[slot] = (uint16_t)v[r];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < ITEMS; ++r) {
+        x[r] = sk[w0 + 64 * r];
+        v[r] = sv[w0 + 64 * r];
+    }
+}
+
 // Equal blocks sorted locally: one work-group sorts a block of consecutive
 // positions in LDS by (segment, key, position), as stable radix passes over
 // 8-bit digits, least significant first: four over the key bits and then, if
@@ -478,45 +518,7 @@ __global__ __launch_bounds__(kTileThreads, 4) void segsort_tile_kernel(TileArgs 
                 }
             }
         }
-        for (int i = t; i < kTileWaves * 128; i += kTileThreads) reinterpret_cast<uint32_t *>(&cnt[0][0])[i] = 0;
-        __syncthreads();
-        int rank[ITEMS];
-#pragma unroll
-        for (int r = 0; r < ITEMS; ++r) {
-            const uint32_t d = (k[r] >> shift) & 255;
-            const uint64_t same = match_digit(d);
-            const int before = lanes_before(same);
-            const int c = cnt[wid][d];
-            rank[r] = c + before;
-            if (before == 0) cnt[wid][d] = (uint16_t)(c + __popcll(same));
-        }
-        __syncthreads();
-        int mine = 0, total;
-        if (t < 256)
-#pragma unroll
-            for (int w = 0; w < kTileWaves; ++w) mine += cnt[w][t];
-        int at = wg_scan_incl<kTileThreads>(mine, wsum, &total) - mine;
-        if (t < 256) {
-#pragma unroll
-            for (int w = 0; w < kTileWaves; ++w) {
-                const int c = cnt[w][t];
-                cnt[w][t] = (uint16_t)at;
-                at += c;
-            }
-        }
-        __syncthreads();
-#pragma unroll
-        for (int r = 0; r < ITEMS; ++r) {
-            const int slot = cnt[wid][(k[r] >> shift) & 255] + rank[r];
-            sk[slot] = k[r];
-            sv[slot] = (uint16_t)v[r];
-        }
-        __syncthreads();
-#pragma unroll
-        for (int r = 0; r < ITEMS; ++r) {
-            k[r] = sk[w0 + 64 * r];
-            v[r] = sv[w0 + 64 * r];
-        }
+        lds_radix_pass<kTileThreads, ITEMS>(k, v, shift, sk, sv, cnt, wsum);
     }
     // the words are key bits if the block holds one segment
     const long s0 = num == 1 ? seg_at(a.off, lo, a.n) : 0;
@@ -957,6 +959,8 @@ hipError_t launch_segsort(const float *keys, const int32_t *off, int S, long n, 
 
 constexpr int kNmsMax = MIVISION_NMS_MAX_CANDIDATES;
 
+constexpr int kNmsChunk = 1024;       // input rows per work-group of the collecting kernel
+
 struct NmsArgs {
     const float *data;
     float *out;
@@ -966,67 +970,259 @@ struct NmsArgs {
     int mrows;         // mask rows per image: 64 * capw
     float overlap, valid;
     int id_index, score_index, coord_start, force;
-    const int32_t *pos;       // [B][N] exclusive scan of the candidate flags
-    const int32_t *seg_off;   // [B + 1] first compacted slot of each image; seg_off[B] = all candidates
-    float *ckey;              // [B*N] compacted scores
-    int32_t *corig;           // [B*N] compacted row index within the image
-    int32_t *rank;            // [B*N] segmented argsort of ckey: rank r of image b -> local slot
+    int chunks;        // per image
+    uint32_t *ckey;           // [B][N]: each chunk's candidates from its first row's slot on: key bits
+    int32_t *corig;           // and input rows, in row order
+    int32_t *ccount;          // [B][chunks] candidates of each chunk
+    int32_t *count;           // [B] compared candidates
     float4 *cbox;             // [B][mrows] box of the candidate of rank r
     float *ccls;              // [B][mrows] its class
     int32_t *crow;            // [B][mrows] its input row
     uint64_t *mask;           // [B][mrows][capw]
 };
 
-// Every value of out is set invalid first (Sec. 4.3): no per-row decision.
-__global__ __launch_bounds__(256) void nms_fill_kernel(float *out, long count)
+// First pass over the rows, one work-group per chunk of 1024: every value of
+// out is set invalid (Sec. 4.3: no per-row decision), and the chunk's
+// candidates leave as (descending key bits, row), in row order.  No slot
+// depends on another chunk, so no scan over the image is needed first (a
+// three-stage scan of the candidate flags, one work-group per image, took 12
+// us for 24564 rows, and a compaction launch 3).
+__global__ __launch_bounds__(256) void nms_collect_kernel(NmsArgs a)
 {
-    const long i0 = ((long)blockIdx.x * 256 + threadIdx.x) * 4;
-    if (((uintptr_t)out & 15) == 0 && i0 + 3 < count) {
-        *reinterpret_cast<float4 *>(out + i0) = make_float4(-1.f, -1.f, -1.f, -1.f);
-        return;
+    __shared__ int found[16];
+    const int t = threadIdx.x, lane = t & 63, wid = t >> 6;
+    const int b = blockIdx.x / a.chunks;
+    const int chunk = blockIdx.x - b * a.chunks;
+    const int r0 = chunk * kNmsChunk;
+    const int rows = a.N - r0 < kNmsChunk ? a.N - r0 : kNmsChunk;
+    const long first = (long)b * a.N + r0;
+    float s[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int r = t + 256 * j;
+        s[j] = r < rows ? a.data[(first + r) * a.width + a.score_index] : 0.f;
     }
-    for (long i = i0; i < i0 + 4 && i < count; ++i) out[i] = -1.f;
+    float *o = a.out + first * a.width;
+    const int vals = rows * a.width;
+    const int lead = min(vals, (int)((16 - ((uintptr_t)o & 15)) & 15) / 4);   // up to 16-byte alignment
+    const int quads = (vals - lead) / 4;
+    for (int i = t; i < quads; i += 256) reinterpret_cast<float4 *>(o + lead)[i] = make_float4(-1.f, -1.f, -1.f, -1.f);
+    if (t < lead) o[t] = -1.f;
+    if (t < vals - lead - 4 * quads) o[lead + 4 * quads + t] = -1.f;
+
+    uint64_t bal[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        bal[j] = __ballot(t + 256 * j < rows && s[j] > a.valid);
+        if (lane == 0) found[4 * j + wid] = __popcll(bal[j]);
+    }
+    __syncthreads();
+    int before[4], total = 0;               // candidates in earlier rounds and wavefronts
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        if ((i & 3) == wid) before[i >> 2] = total;
+        total += found[i];
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+        if (bal[j] >> lane & 1) {
+            const long slot = first + before[j] + lanes_before(bal[j]);
+            a.ckey[slot] = key_bits(s[j], 1);
+            a.corig[slot] = r0 + t + 256 * j;
+        }
+    if (t == 0) a.ccount[blockIdx.x] = total;
 }
 
-// Candidate rows move to their compacted slots, image after image.
-__global__ __launch_bounds__(256) void nms_compact_kernel(NmsArgs a)
+__device__ __forceinline__ float4 load_box(const NmsArgs &a, int b, int i, float *cls)
 {
-    const long g = (long)blockIdx.x * 256 + threadIdx.x;
-    if (g >= (long)a.B * a.N) return;
-    const int b = (int)(g / a.N), i = (int)(g - (long)b * a.N);
-    const float s = a.data[g * a.width + a.score_index];
-    if (!(s > a.valid)) return;
-    const long total = (long)a.B * a.N;
-    long slot = (long)a.seg_off[b] + a.pos[g];
-    if (slot < 0 || slot >= total) return;
-    a.ckey[slot] = s;
-    a.corig[slot] = i;
+    const float *row = a.data + ((long)b * a.N + i) * a.width;
+    *cls = a.id_index >= 0 ? row[a.id_index] : 0.f;
+    const float *c = row + a.coord_start;
+    return make_float4(c[0], c[1], c[2], c[3]);
 }
 
-// Candidates of image b: count, and the input row of rank r.
-__device__ __forceinline__ int nms_count(const NmsArgs &a, int b)
+// The best cand_max candidates of an image in rank order, one work-group per
+// image.  If there are more, the key of the last one is found first by
+// counting digits of 11, 11 and 10 bits from the top (radix select), then
+// those above it and the first rows of those equal to it are gathered in row
+// order, and ranked: by comparing each with each (up to 512), or by radix
+// passes in LDS.  Boxes, classes and rows leave in rank order, so that the
+// mask and walk kernels read them with one request each.
+//   One work-group's chain of reads, counts and barriers: 20 us for the best 400
+// of 24564 rows (2400 candidates), where a segmented argsort of all of them
+// and a gathering launch took 31 (box_nms of one image 54 -> 35 us, of 26
+// images of 20565 rows 82 -> 32).
+constexpr int kPickThreads = 1024;
+constexpr int kPickWaves = kPickThreads / 64;
+constexpr int kPickItems = kNmsMax / kPickThreads;     // per thread in the radix passes
+constexpr int kPickCount = 512;                        // most that are ranked by comparing
+
+__global__ __launch_bounds__(kPickThreads) void nms_pick_kernel(NmsArgs a)
 {
-    const long total = (long)a.B * a.N;
-    long s0 = a.seg_off[b], s1 = a.seg_off[b + 1];
-    s0 = s0 < 0 ? 0 : (s0 > total ? total : s0);
-    s1 = s1 < s0 ? s0 : (s1 > total ? total : s1);
-    long c = s1 - s0;
-    c = c < a.N ? c : a.N;   // an image has at most N candidates
-    return (int)(c < a.cand_max ? c : a.cand_max);
+    __shared__ uint32_t key[kNmsMax];                  // picked: key bits, input rows
+    __shared__ int32_t row[kNmsMax];
+    __shared__ uint16_t sv[kNmsMax];
+    __shared__ uint16_t cnt[kPickWaves][256];
+    __shared__ uint32_t hist[2048];
+    __shared__ int wsum[kPickWaves];
+    __shared__ int wlt[kPickWaves], weq[kPickWaves];
+    __shared__ uint32_t s_digit;
+    __shared__ int s_left, s_in;
+    const int t = threadIdx.x, lane = t & 63, wid = t >> 6;
+    const int b = blockIdx.x;
+    const uint32_t *ck = a.ckey + (long)b * a.N;
+    const int32_t *cr = a.corig + (long)b * a.N;
+    const int32_t *cc = a.ccount + (long)b * a.chunks;
+    // wavefront w looks after a contiguous range of chunks
+    const int per = (a.chunks + kPickWaves - 1) / kPickWaves;
+    const int c0 = min(a.chunks, wid * per), c1 = min(a.chunks, c0 + per);
+    auto chunk_count = [&](int c) {                    // never past the chunk's rows
+        const int n = min(kNmsChunk, a.N - c * kNmsChunk);
+        return min(max(cc[c], 0), n);
+    };
+    int mine = 0, total;
+    for (int c = c0 + lane; c < c1; c += 64) mine += chunk_count(c);
+    wg_scan_incl<kPickThreads>(mine, wsum, &total);
+    const int want = min(total, a.cand_max);
+    // last: the largest key that is taken, and how many of its equals are
+    uint32_t last = 0xffffffffu;
+    int equals = total;
+    if (want < total) {
+        uint32_t prefix = 0, known = 0;                // digits found so far, and their mask
+        int left = want;                               // rank of the last among those with the prefix
+#pragma unroll 1
+        for (int p = 0; p < 3; ++p) {
+            const int shift = p == 0 ? 21 : p == 1 ? 10 : 0;
+            const uint32_t dm = p == 2 ? 1023u : 2047u;
+            hist[t] = 0;
+            hist[t + 1024] = 0;
+            __syncthreads();
+            for (int c = c0; c < c1; ++c) {
+                const int n = chunk_count(c);
+                for (int i = lane; i < n; i += 64) {
+                    const uint32_t k = ck[c * kNmsChunk + i];
+                    if ((k & known) == prefix) atomicAdd(&hist[(k >> shift) & dm], 1u);
+                }
+            }
+            __syncthreads();
+            const int h0 = (int)hist[2 * t], h1 = (int)hist[2 * t + 1];
+            int all;
+            const int incl = wg_scan_incl<kPickThreads>(h0 + h1, wsum, &all);
+            const int before = incl - h0 - h1;
+            // the digit whose elements include rank `left` (1-based)
+            if (before < left && left <= before + h0) {
+                s_digit = 2 * t;
+                s_left = left - before;
+                s_in = h0;
+            } else if (before + h0 < left && left <= incl) {
+                s_digit = 2 * t + 1;
+                s_left = left - before - h0;
+                s_in = h1;
+            }
+            __syncthreads();
+            prefix |= s_digit << shift;
+            known |= dm << shift;
+            left = s_left;
+            if (s_in == left) {                        // all of them: no need to tell them apart
+                prefix |= ~known;
+                left = a.N;
+                break;
+            }
+            __syncthreads();
+        }
+        last = prefix;
+        equals = left;
+    }
+    // gather in row order: count per wavefront, then place
+    int lt = 0, eq = 0;
+    for (int c = c0; c < c1; ++c) {
+        const int n = chunk_count(c);
+        for (int i = lane; i < n; i += 64) {
+            const uint32_t k = ck[c * kNmsChunk + i];
+            lt += k < last;
+            eq += k == last;
+        }
+    }
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        lt += __shfl_xor(lt, d);
+        eq += __shfl_xor(eq, d);
+    }
+    if (lane == 0) {
+        wlt[wid] = lt;
+        weq[wid] = eq;
+    }
+    __syncthreads();
+    lt = eq = 0;
+    for (int w = 0; w < wid; ++w) {
+        lt += wlt[w];
+        eq += weq[w];
+    }
+    for (int c = c0; c < c1; ++c) {
+        const int n = chunk_count(c);
+        for (int i0 = 0; i0 < n; i0 += 64) {
+            const int i = i0 + lane;
+            const uint32_t k = i < n ? ck[c * kNmsChunk + i] : 0xffffffffu;
+            const int32_t r = i < n ? cr[c * kNmsChunk + i] : 0;
+            const uint64_t bl = __ballot(i < n && k < last), be = __ballot(i < n && k == last);
+            const int nl = lt + lanes_before(bl), ne = eq + lanes_before(be);
+            const bool take = i < n && (k < last || (k == last && ne < equals));
+            const int slot = nl + min(ne, equals);
+            if (take && slot < want) {
+                key[slot] = k;
+                row[slot] = min(max(r, 0), a.N - 1);
+            }
+            lt += __popcll(bl);
+            eq += __popcll(be);
+        }
+    }
+    __syncthreads();
+    auto emit = [&](int rank, int i) {
+        float c;
+        const long o = (long)b * a.mrows + rank;
+        a.cbox[o] = load_box(a, b, row[i], &c);
+        a.ccls[o] = c;
+        a.crow[o] = row[i];
+    };
+    if (want <= kPickCount) {
+        // rank = how many come before: two threads per candidate, half each
+        int *rank = reinterpret_cast<int *>(hist);
+        if (t < kPickCount) rank[t] = 0;
+        __syncthreads();
+        const int i = t & (kPickCount - 1), half = (want + 1) / 2;
+        const int j0 = t < kPickCount ? 0 : half, j1 = t < kPickCount ? half : want;
+        if (i < want) {
+            const uint32_t k = key[i];
+            int n = 0;
+#pragma unroll 8
+            for (int j = j0; j < j1; ++j) n += key[j] < k || (key[j] == k && j < i);
+            atomicAdd(&rank[i], n);
+        }
+        __syncthreads();
+        if (t < want) emit(rank[t], t);
+    } else {
+        uint32_t x[kPickItems];
+        int v[kPickItems];
+#pragma unroll
+        for (int r = 0; r < kPickItems; ++r) {
+            v[r] = wid * 64 * kPickItems + lane + 64 * r;
+            x[r] = v[r] < want ? key[v[r]] : 0xffffffffu;     // the rest last
+        }
+        __syncthreads();
+#pragma unroll 1
+        for (int p = 0; p < 4; ++p)
+            lds_radix_pass<kPickThreads, kPickItems>(x, v, 8 * p, key, sv, cnt, wsum);
+#pragma unroll
+        for (int r = 0; r < kPickItems; ++r) {
+            const int rank = wid * 64 * kPickItems + lane + 64 * r;
+            if (rank < want) emit(rank, v[r]);
+        }
+    }
+    if (t == 0) a.count[b] = want;
 }
 
-__device__ __forceinline__ int nms_row(const NmsArgs &a, int b, int r)
-{
-    const long total = (long)a.B * a.N;
-    long s0 = a.seg_off[b];
-    s0 = s0 < 0 ? 0 : (s0 > total ? total : s0);
-    long li = a.rank[s0 + r];                     // r < count: s0 + r < total
-    li = li < 0 ? 0 : li;
-    long slot = s0 + li;
-    slot = slot < total ? slot : total - 1;
-    const int i = a.corig[slot];
-    return i < 0 ? 0 : (i >= a.N ? a.N - 1 : i);
-}
+// Compared candidates of image b.
+__device__ __forceinline__ int nms_count(const NmsArgs &a, int b) { return min(max(a.count[b], 0), a.cand_max); }
 
 // IoU of two corner-encoded boxes, each operation rounded to fp32 in the
 // order of the definition.  Contraction into fused multiply-adds is switched
@@ -1043,30 +1239,6 @@ __device__ __forceinline__ float box_iou(float4 p, float4 q)
     const float aq = fmaxf(0.f, q.z - q.x) * fmaxf(0.f, q.w - q.y);
     const float uni = (ap + aq) - inter;
     return uni <= 0.f ? 0.f : inter / uni;
-}
-
-__device__ __forceinline__ float4 load_box(const NmsArgs &a, int b, int i, float *cls)
-{
-    const float *row = a.data + ((long)b * a.N + i) * a.width;
-    *cls = a.id_index >= 0 ? row[a.id_index] : 0.f;
-    const float *c = row + a.coord_start;
-    return make_float4(c[0], c[1], c[2], c[3]);
-}
-
-// The compared candidates in rank order: box, class and input row of rank r
-// of image b (r < the image's candidate count), gathered once so that the
-// mask and walk kernels read them with one request each.
-__global__ __launch_bounds__(256) void nms_gather_kernel(NmsArgs a)
-{
-    const int b = blockIdx.y;
-    const int r = blockIdx.x * 256 + threadIdx.x;
-    if (r >= nms_count(a, b)) return;
-    const int i = nms_row(a, b, r);
-    float c;
-    const long k = (long)b * a.mrows + r;
-    a.cbox[k] = load_box(a, b, i, &c);
-    a.ccls[k] = c;
-    a.crow[k] = i;
 }
 
 // Suppression masks: work-group (column block cb, row block rb, image b),
@@ -1194,7 +1366,7 @@ __global__ __launch_bounds__(kSweepThreads) void nms_sweep_kernel(NmsArgs a)
 }
 
 struct NmsLayout {
-    long pos, seg_off, ckey, corig, rank, sort, cbox, ccls, crow, mask, total;
+    long ckey, corig, ccount, count, cbox, ccls, crow, mask, total;
 };
 
 NmsLayout nms_layout(int B, int N, int cap)
@@ -1203,18 +1375,14 @@ NmsLayout nms_layout(int B, int N, int cap)
     const int capw = (cap + 63) / 64;
     NmsLayout l{};
     long o = 0;
-    l.pos = o;
-    o += align256(n * 4);
-    l.seg_off = o;
-    o += align256((long)(B + 1) * 4);
     l.ckey = o;
     o += align256(n * 4);
     l.corig = o;
     o += align256(n * 4);
-    l.rank = o;
-    o += align256(n * 4);
-    l.sort = o;
-    o += align256(argsort_ws_bytes(n));
+    l.ccount = o;
+    o += align256((long)B * ((N + kNmsChunk - 1) / kNmsChunk) * 4);
+    l.count = o;
+    o += align256((long)B * 4);
     const long mrows = (long)B * capw * 64;
     l.cbox = o;
     o += align256(mrows * 16);
@@ -1321,39 +1489,23 @@ int vision_box_nms(int batch, int num, int width, const float *data, float *out,
     a.score_index = score_index;
     a.coord_start = coord_start;
     a.force = force_suppress != 0;
-    a.pos = reinterpret_cast<int32_t *>(w + l.pos);
-    a.seg_off = reinterpret_cast<int32_t *>(w + l.seg_off);
-    a.ckey = reinterpret_cast<float *>(w + l.ckey);
+    a.chunks = (num + kNmsChunk - 1) / kNmsChunk;
+    a.ckey = reinterpret_cast<uint32_t *>(w + l.ckey);
     a.corig = reinterpret_cast<int32_t *>(w + l.corig);
-    a.rank = reinterpret_cast<int32_t *>(w + l.rank);
+    a.ccount = reinterpret_cast<int32_t *>(w + l.ccount);
+    a.count = reinterpret_cast<int32_t *>(w + l.count);
     a.cbox = reinterpret_cast<float4 *>(w + l.cbox);
     a.ccls = reinterpret_cast<float *>(w + l.ccls);
     a.crow = reinterpret_cast<int32_t *>(w + l.crow);
     a.mask = reinterpret_cast<uint64_t *>(w + l.mask);
-    const long n = (long)batch * num;
-    const long vals = n * width;
-    hipError_t e;
-    launch_kernel(nms_fill_kernel, dim3((unsigned)((vals + 1023) / 1024)), dim3(256), 0, st, out, vals);
-    // slots of the candidates within each image, and the candidate count per image
-    int32_t *pos = reinterpret_cast<int32_t *>(w + l.pos);
-    int32_t *seg = reinterpret_cast<int32_t *>(w + l.seg_off);
-    if ((e = launch_scan(SrcScore{data, width, score_index, valid_thresh}, batch, (long)num, pos, true, seg + 1,
-                         nullptr, st)) != hipSuccess)
-        return set_hip_error(e);
-    // first slot of each image: exclusive scan of the counts; seg[B] = all
-    if ((e = launch_scan(SrcI32{seg + 1}, 1, (long)batch, seg, true, seg + batch, nullptr, st)) != hipSuccess)
-        return set_hip_error(e);
-    launch_kernel(nms_compact_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, a);
-    if ((e = launch_segsort(a.ckey, seg, batch, n, 1, a.rank, w + l.sort, st)) != hipSuccess)
-        return set_hip_error(e);
+    launch_kernel(nms_collect_kernel, dim3((unsigned)((long)batch * a.chunks)), dim3(256), 0, st, a);
     if (a.capw > 0) {   // topk == 0: no candidate, the output stays invalid
-        launch_kernel(nms_gather_kernel, dim3((unsigned)((a.mrows + 255) / 256), (unsigned)batch), dim3(256), 0, st,
-                      a);
+        launch_kernel(nms_pick_kernel, dim3((unsigned)batch), dim3(kPickThreads), 0, st, a);
         launch_kernel(nms_mask_kernel, dim3((unsigned)a.capw, (unsigned)a.capw, (unsigned)batch), dim3(256), 0, st,
                       a);
         launch_kernel(nms_sweep_kernel, dim3((unsigned)batch), dim3(kSweepThreads), 0, st, a);
     }
-    e = hipGetLastError();
+    const hipError_t e = hipGetLastError();
     return e == hipSuccess ? MICONV_OK : set_hip_error(e);
 }
 

@@ -190,6 +190,29 @@ def test_box_nms_bitwise(oracle_lib, case):
     assert kept.min() > 0 if topk != 0 else kept.max() == 0
 
 
+PICK_CASES = [   # (batch, num, topk, scores): chunks of 1024 rows, ranking by comparing up to 512, else by radix passes
+    (3, 1023, 512, "ties"), (2, 1025, 513, "ties"), (1, 1, 5, "plain"), (4, 3000, 64, "ties"), (2, 9000, 4096, "plain"),
+    (2, 5000, 400, "inf"), (3, 2500, 100, "nan"), (1, 4096, 4096, "ties"), (2, 700, 1000, "nan"),
+]
+
+
+@pytest.mark.parametrize("case", PICK_CASES, ids=["-".join(map(str, c)) for c in PICK_CASES])
+def test_box_nms_pick_bitwise(oracle_lib, case):
+    """The best topk of more candidates than that: equal scores at the cut
+    (taken in row order), infinite scores, NaN scores (never candidates)."""
+    B, N, topk, scores = case
+    data = det.detection_rows(B, N, classes=5, objects=8, seed=N + topk, object_frac=0.3)
+    u = np.random.default_rng(N).uniform(size=(B, N))
+    if scores == "ties":
+        data[..., 1] = np.round(data[..., 1] * 8) / 8 + 0.02
+    elif scores == "inf":
+        data[..., 1] = np.where(u < 0.5, np.inf, data[..., 1])
+    elif scores == "nan":
+        data[..., 1] = np.where(u < 0.1, np.nan, data[..., 1] - 0.2)
+    for valid in (0.01, -1.0):
+        _check_nms(oracle_lib, data, overlap_thresh=0.45, valid_thresh=valid, topk=topk)
+
+
 def test_box_nms_iou_rounding_at_threshold(oracle_lib):
     """4096 images of two same-class boxes whose IoU lies within a few ulps
     of the 0.5 threshold (B is A shifted right by about a third of its
