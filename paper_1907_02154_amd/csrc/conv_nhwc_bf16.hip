@@ -16,6 +16,7 @@
 // is KRC channels at one filter position), so the chunk's (r, s) is uniform.
 #include "internal.h"
 
+#include <algorithm>
 #include <cstdio>
 
 namespace miconv {
@@ -745,6 +746,8 @@ __device__ inline void epilogue_cl(const ConvArgs &a, const floatx16 (&acc)[BJ][
 // channel row, each lane fetching the pixel pair its LDS dword holds under
 // the unit permutation.  Same bandwidth per byte through the load path,
 // 4x the instructions.
+constexpr int kPpRows = 224;   // patch rows of igemm_bf16_pp_kernel: 128 + 2W + 2, and a row of zeros
+
 template <int R_, int S_, int BPX, int BKC, int WPX, int WCH, int NST, int NCHWB, int KRC, bool RES, bool YCL>
 __device__ __forceinline__ void dma_body(const ConvArgs &a)
 {
@@ -1350,6 +1353,356 @@ __global__ __launch_bounds__(64 * WPX * WCH) void igemm_bf16_halo_cl_kernel(Conv
     halo_body<BPX, BKC, WPX, WCH, PR, NPB, false, true>(a);
 }
 
+// 3x3, stride 1, padding 1 on 128 x 128 tiles with eight wavefronts in two
+// groups of four that alternate: while one multiplies a chunk (at raised
+// priority), the other reads the next chunk's operands from LDS into its
+// registers and makes its requests, and a barrier swaps the roles.  Every
+// chunk belongs to one group (even chunks 0, odd 1), so each holds the sums of
+// half the reduction; they are added in the epilogue.
+//   Patches and filters as in igemm_bf16_halo_kernel (packed filters in
+// 64-channel blocks, patch rows m0-W-1 ..), with a ring of five filter stages
+// and two patches: 136 KB of LDS, one work-group per CU.  A group requests its
+// own chunk four ahead, and one seventh of the next channel block's patch with
+// each of the first seven taps; it waits for both at the end of its next
+// reading phase.
+//   What bounds it: the reading phase.  Its 64 KB of operands and 20 KB of
+// incoming requests take about 770 cycles of LDS, beside the MFMAs' 512; a
+// chunk measures 0.42 us (880 cycles), plus 10 us a launch for the first
+// patch, the epilogue and the filter pack.  The wavefront that reads is alone
+// with its instructions, so the addresses of the next phase are computed
+// between the MFMAs, taps that fall into the padding read a row of zeros
+// (chosen by a 9-bit mask per pixel), and the requests' addresses are a
+// constant per lane plus a scalar: with all that in the reading phase it took
+// 1500 cycles; with the requests between the MFMAs too, 20% more than now.
+// Batch 64, 14x14, 256 -> 256 (14.8 GFLOP): 32 us on the 128 x 64 direct tiles,
+// 22 us here.
+//   256 x 128 tiles (128 x 64 per wavefront, a quarter fewer LDS reads, the
+// groups on halves of each chunk) measured 0.75 us a chunk of twice the work,
+// but 15 us a launch around it: 28x28 128 -> 128 at batch 64 31.5 us against
+// the halo kernel's 25.3.
+template <bool YCL>
+__global__ __launch_bounds__(512, 2) void igemm_bf16_pp_kernel(ConvArgs a)
+{
+    constexpr int BPX = 128, BKC = 128, PR = kPpRows;
+    constexpr int NA = 5, D = NA - 1;                   // filter stages, chunks requested ahead
+    constexpr int UA = BKC * 8, UP = PR * 8;            // 16-byte units per filter stage, per patch
+    constexpr int LA = UA / 256;                        // filter loads per lane of a group
+    constexpr int PIECES = PR / 32;                     // patch loads per lane of a group, one per tap
+    static_assert(PIECES <= 7, "a piece is read no sooner than three phases after its request");
+    constexpr int BJ = 2, BI = 2;                       // 64 x 64 wavefront tiles, 2 x 2 of them
+    constexpr int CP = 132;                             // epilogue row pitch (floats)
+    constexpr int SMEM = NA * UA + 2 * UP > 2 * 128 * CP / 4 ? NA * UA + 2 * UP : 2 * 128 * CP / 4;
+    __shared__ __attribute__((aligned(128))) uint4 smem[SMEM];
+
+    const uint16_t *__restrict__ xcl = static_cast<const uint16_t *>(a.x);   // [N][H][W][C]
+    const uint16_t *__restrict__ wp = static_cast<const uint16_t *>(a.w);    // [K][Cg/64][3][3][64]
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int grp = wid >> 2, w4 = wid & 3;             // group, wavefront of it
+    const int gt = tid & 255;                           // thread of the group
+    const int wpx = w4 & 1, wch = w4 >> 1;
+    const int h = lane >> 5, ll = lane & 31;
+    // XCD-aware tile order, as in igemm_bf16_dma_kernel
+    const int T = gridDim.x;
+    const int xcd = blockIdx.x % 8, jx = blockIdx.x / 8;
+    const int L = xcd * (T / 8) + min(xcd, T % 8) + jx;
+    const int ktiles = (a.Kg + BKC - 1) / BKC;
+    const int mtiles = (a.M + BPX - 1) / BPX;
+    const int ky = L % ktiles;
+    const int mx = (L / ktiles) % mtiles;
+    const int z = L / (ktiles * mtiles);
+    const int g = z % a.groups;
+    const int split = z / a.groups;
+    const int m0 = mx * BPX;
+    const int k0 = ky * BKC;
+    const int t0 = split * a.kr_per_split / 64;         // a multiple of nine chunks
+    const int n = min(a.Kred, (split + 1) * a.kr_per_split) / 64 - t0;
+    const int prow = BPX + 2 * a.W + 2;
+    if (prow >= PR) return;                             // the launcher never sends such a layer
+
+    constexpr unsigned kOutside = 0x80000000u;          // past either buffer, whatever is added: zeros
+    const __amdgpu_buffer_rsrc_t wres = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<uint16_t *>(wp), (short)0, (int)((long)a.K * a.Kred * 2), 0x00020000);
+    const __amdgpu_buffer_rsrc_t xres = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<uint16_t *>(xcl), (short)0, (int)((long)a.N * a.H * a.W * a.C * 2), 0x00020000);
+
+    // Filters: load i of a group's thread fills unit i*256 + gt of a stage.
+    unsigned aoffs[LA];
+#pragma unroll
+    for (int i = 0; i < LA; ++i) {
+        const int u = i * 256 + gt;
+        const int row = u >> 3;
+        const int k = k0 + row;
+        aoffs[i] = k < a.Kg ? (unsigned)((((long)g * a.Kg + k) * a.Kred + ((u & 7) ^ unit_swz(row)) * 8) * 2) : kOutside;
+    }
+    auto issue_a = [&](int c, int stage) {
+        uint4 *st = smem + stage * UA + w4 * 64;
+        const int soff = 128 * (t0 + c);
+#pragma unroll
+        for (int i = 0; i < LA; ++i)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(wres, (lds_void_t *)(st + i * 256), 16, aoffs[i], soff, 0, 0);
+    };
+    // Patch piece i: rows 32 i .. 32 i + 31, by one group.  The last row used
+    // is followed by rows of zeros (row PR - 1 is one).
+    const int prl = gt >> 3;                            // row of piece 0
+    const int pgm = m0 - a.W - 1 + prl;                 // its pixel
+    const int plim = min(a.M, m0 - a.W - 1 + prow);     // pixels from here on load as zeros
+    const unsigned poff = (unsigned)((pgm * a.C + g * a.Cg + ((gt & 7) ^ unit_swz(prl)) * 8) * 2);
+    auto issue_piece = [&](int cb, int i) {
+        uint4 *pb = smem + NA * UA + (cb & 1) * UP + i * 256 + w4 * 64;
+        const bool ok = (unsigned)(pgm + 32 * i) < (unsigned)plim;
+        const unsigned off = ok ? poff + 64u * i * a.C + 128u * cb : kOutside;
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(xres, (lds_void_t *)pb, 16, off, 0, 0, 0);
+    };
+
+    // Taps inside the image, one bit each, of this lane's output pixels.
+    unsigned inside[BJ];
+#pragma unroll
+    for (int bj = 0; bj < BJ; ++bj) {
+        const int m = m0 + wpx * 64 + bj * 32 + ll;
+        const int mm = m < a.M ? m : 0;
+        const int pq = mm - (int)fdiv(mm, a.dv_pq) * a.PQ;
+        const int p = fdiv(pq, a.dv_q);
+        const int q = pq - p * a.Q;
+        const unsigned rows = (p > 0 ? 0x007u : 0u) | 0x038u | (p + 1 < a.H ? 0x1c0u : 0u);
+        const unsigned cols = (q > 0 ? 0x049u : 0u) | 0x092u | (q + 1 < a.W ? 0x124u : 0u);
+        inside[bj] = m < a.M ? rows & cols : 0u;
+    }
+    // LDS byte addresses of unit h (the other reduction steps' units: xor 32 ks).
+    const char *lds = reinterpret_cast<const char *>(smem);
+    const int fbase = (wch * 64 + ll) * 128 + ((h ^ unit_swz(ll)) << 4);
+    int fa;
+    int xa[BJ];
+    auto addresses = [&](int stage, int cb, int tap) {  // of the operands of a chunk
+        fa = fbase + stage * UA * 16;
+        const int rs = (tap >= 6 ? 2 * a.W - 6 : tap >= 3 ? a.W - 3 : 0) + tap;
+#pragma unroll
+        for (int bj = 0; bj < BJ; ++bj) {
+            const int row = (inside[bj] >> tap) & 1 ? wpx * 64 + bj * 32 + ll + rs : PR - 1;
+            xa[bj] = NA * UA * 16 + (cb & 1) * UP * 16 + row * 128 + ((h ^ unit_swz(row)) << 4);
+        }
+    };
+
+    floatx16 acc[BJ][BI];
+#pragma unroll
+    for (int bj = 0; bj < BJ; ++bj)
+#pragma unroll
+        for (int bi = 0; bi < BI; ++bi)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[bj][bi][v] = 0.f;
+
+    // Prologue: the first patch, its pieces dealt to the groups in turn, and
+    // each group's first two chunks.
+    int cb = t0 / 9, tap = grp;                         // of the group's next chunk
+#pragma unroll
+    for (int i = 0; i < PIECES; ++i)
+        if (grp == (i & 1)) issue_piece(cb, i);
+    issue_a(grp, grp);
+    issue_a(grp + 2, grp + 2);
+    wait_vmcnt<LA>();                                   // the patch and the group's first chunk
+
+    bf16x8 wv[4][BI], xv[4][BJ];
+    auto swap_roles = [&] {
+        __builtin_amdgcn_sched_barrier(0);
+        asm volatile("s_barrier" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    swap_roles();
+    int stage = grp, fill = (grp + D) % NA;             // of the group's next chunk, and of the one D later
+    addresses(stage, cb, tap);
+    if (grp) swap_roles();
+    for (int p = grp; p <= n; p += 2) {
+        if (p < n) {
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks) {
+                const char *f = lds + (fa ^ (32 * ks));
+#pragma unroll
+                for (int bi = 0; bi < BI; ++bi) wv[ks][bi] = *reinterpret_cast<const bf16x8 *>(f + bi * 4096);
+#pragma unroll
+                for (int bj = 0; bj < BJ; ++bj)
+                    xv[ks][bj] = *reinterpret_cast<const bf16x8 *>(lds + (xa[bj] ^ (32 * ks)));
+            }
+            // the group's requests of its last reading phase (chunk p + 2 and
+            // a patch piece) have landed once only this phase's are outstanding
+            if (p + D < n) {
+                issue_a(p + D, fill);
+                if (tap < PIECES) {
+                    issue_piece(cb + 1, tap);
+                    wait_vmcnt<LA + 1>();
+                } else {
+                    wait_vmcnt<LA>();
+                }
+            } else {
+                wait_vmcnt<0>();
+            }
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        }
+        swap_roles();
+        if (p + 1 <= n) {
+            if (p < n) {
+                stage = stage + 2 >= NA ? stage + 2 - NA : stage + 2;
+                fill = fill + 2 >= NA ? fill + 2 - NA : fill + 2;
+                tap += 2;
+                if (tap >= 9) {
+                    tap -= 9;
+                    ++cb;
+                }
+                __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+                for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+                    for (int bj = 0; bj < BJ; ++bj)
+#pragma unroll
+                        for (int bi = 0; bi < BI; ++bi) {
+                            if constexpr (YCL)
+                                acc[bj][bi] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wv[ks][bi], xv[ks][bj],
+                                                                                     acc[bj][bi], 0, 0, 0);
+                            else
+                                acc[bj][bi] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xv[ks][bj], wv[ks][bi],
+                                                                                     acc[bj][bi], 0, 0, 0);
+                        }
+                addresses(stage, cb, tap);
+                __builtin_amdgcn_s_setprio(0);
+            }
+            swap_roles();
+        }
+    }
+
+    // Epilogue: both groups' tiles in LDS, [128 pixels][128 filters] (YCL) or
+    // [128 filters][128 pixels]; summed as they are read back.
+    __syncthreads();
+    float *ot = reinterpret_cast<float *>(smem) + grp * 128 * CP;
+#pragma unroll
+    for (int bi = 0; bi < BI; ++bi)
+#pragma unroll
+        for (int bj = 0; bj < BJ; ++bj)
+#pragma unroll
+            for (int q4 = 0; q4 < 4; ++q4) {
+                const float4 v = make_float4(acc[bj][bi][4 * q4], acc[bj][bi][4 * q4 + 1], acc[bj][bi][4 * q4 + 2],
+                                             acc[bj][bi][4 * q4 + 3]);
+                // four consecutive filters of a pixel (YCL), or pixels of a filter
+                const int major = YCL ? wpx * 64 + bj * 32 + ll : wch * 64 + bi * 32 + ll;
+                const int minor = (YCL ? wch * 64 + bi * 32 : wpx * 64 + bj * 32) + 8 * q4 + 4 * h;
+                *reinterpret_cast<float4 *>(ot + major * CP + minor) = v;
+            }
+    __syncthreads();
+    const float *o0 = reinterpret_cast<const float *>(smem), *o1 = o0 + 128 * CP;
+    const bool split_out = a.splits > 1;
+    if constexpr (YCL) {
+        const int o = tid & 15;
+        const int k = k0 + 8 * o;
+        const int kg = g * a.Kg + k;
+        if (k >= a.Kg) return;                          // K/groups % 8 == 0: the octet is whole
+        float bv[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) bv[e] = !split_out && a.bias ? a.bias[kg + e] : 0.f;
+        const uint16_t *res = reinterpret_cast<const uint16_t *>(a.res);
+        uint16_t *y = reinterpret_cast<uint16_t *>(a.y);
+#pragma unroll
+        for (int it = 0; it < 4; ++it) {
+            const int pl = (tid >> 4) + 32 * it;
+            const int m = m0 + pl;
+            if (m >= a.M) break;
+            const long off = (long)m * a.K + kg;
+            uint32_t rr[4] = {0, 0, 0, 0};
+            if (res && !split_out) {
+                const uint4 rq = *reinterpret_cast<const uint4 *>(res + off);
+                rr[0] = rq.x;
+                rr[1] = rq.y;
+                rr[2] = rq.z;
+                rr[3] = rq.w;
+            }
+            float v[8];
+#pragma unroll
+            for (int e = 0; e < 8; e += 4) {
+                const float4 lo = *reinterpret_cast<const float4 *>(o0 + pl * CP + 8 * o + e);
+                const float4 hi = *reinterpret_cast<const float4 *>(o1 + pl * CP + 8 * o + e);
+                v[e] = lo.x + hi.x;
+                v[e + 1] = lo.y + hi.y;
+                v[e + 2] = lo.z + hi.z;
+                v[e + 3] = lo.w + hi.w;
+            }
+            if (split_out) {
+                float *dst = a.ws + (long)split * a.M * a.K + off;
+                *reinterpret_cast<float4 *>(dst) = make_float4(v[0], v[1], v[2], v[3]);
+                *reinterpret_cast<float4 *>(dst + 4) = make_float4(v[4], v[5], v[6], v[7]);
+                continue;
+            }
+            uint32_t d[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                float v0 = v[2 * e] + bv[2 * e], v1 = v[2 * e + 1] + bv[2 * e + 1];
+                if (res) {
+                    v0 += bf16_to_f32((uint16_t)(rr[e] & 0xFFFFu));
+                    v1 += bf16_to_f32((uint16_t)(rr[e] >> 16));
+                }
+                if (a.relu) {
+                    v0 = fmaxf(v0, 0.f);
+                    v1 = fmaxf(v1, 0.f);
+                }
+                d[e] = pack_bf16x2(v0, v1);
+            }
+            *reinterpret_cast<uint4 *>(y + off) = make_uint4(d[0], d[1], d[2], d[3]);
+        }
+    } else {
+        float *out = split_out ? a.ws + (long)split * a.K * a.M : a.y;
+        const bool vec =
+            split_out ? (a.M & 3) == 0
+                      : (a.PQ & 3) == 0 && (((uintptr_t)a.y | (uintptr_t)a.res) & 15) == 0 && (a.ysn & 3) == 0;
+        const int c4 = tid & 31;                        // quad of pixels; filters tid / 32 + 16 i
+        const int m = m0 + 4 * c4;
+        if (m >= a.M) return;
+        const int im = split_out ? 0 : (int)fdiv(m, a.dv_pq);
+        const long kstride = split_out ? (long)a.M : (long)a.PQ;
+        const long base = split_out ? (long)m : (long)im * a.ysn + (m - im * a.PQ);
+        const bool quad = vec && m + 3 < a.M;           // in one image plane (P*Q % 4 == 0)
+#pragma unroll 4
+        for (int kl = tid >> 5; kl < BKC; kl += 16) {
+            const int k = k0 + kl;
+            if (k >= a.Kg) break;
+            const int kg = g * a.Kg + k;
+            const float4 lo = *reinterpret_cast<const float4 *>(o0 + kl * CP + 4 * c4);
+            const float4 hi = *reinterpret_cast<const float4 *>(o1 + kl * CP + 4 * c4);
+            float ve[4] = {lo.x + hi.x, lo.y + hi.y, lo.z + hi.z, lo.w + hi.w};
+            const float bv = !split_out && a.bias ? a.bias[kg] : 0.f;
+            if (quad) {
+                const long off = base + kg * kstride;
+                if (!split_out) {
+                    float4 rq = make_float4(0.f, 0.f, 0.f, 0.f);
+                    if (a.res) rq = *reinterpret_cast<const float4 *>(a.res + off);
+                    const float re[4] = {rq.x, rq.y, rq.z, rq.w};
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        ve[e] += bv;
+                        if (a.res) ve[e] += re[e];
+                        if (a.relu) ve[e] = fmaxf(ve[e], 0.f);
+                    }
+                }
+                typedef float f32x4 __attribute__((ext_vector_type(4)));
+                const f32x4 nv = {ve[0], ve[1], ve[2], ve[3]};
+                __builtin_nontemporal_store(nv, reinterpret_cast<f32x4 *>(out + off));
+                continue;
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int mm = m + e;
+                if (mm >= a.M) break;
+                const int ne = split_out ? 0 : (int)fdiv(mm, a.dv_pq);
+                const long off =
+                    split_out ? (long)kg * a.M + mm : (long)ne * a.ysn + (long)kg * a.PQ + (mm - ne * a.PQ);
+                float val = ve[e];
+                if (!split_out) {
+                    val += bv;
+                    if (a.res) val += a.res[off];
+                    if (a.relu) val = fmaxf(val, 0.f);
+                }
+                out[off] = val;
+            }
+        }
+    }
+}
+
 template <int R_, int S_, int BPX, int BKC, int WPX, int WCH, int NST, int NCHWB, int KRC = 64>
 void launch_dma(const ConvArgs &a, dim3 grid, hipStream_t st)
 {
@@ -1537,6 +1890,18 @@ hipError_t launch_halo(const ConvArgs &a, int bkc, int pr, dim3 grid, hipStream_
     return hipSuccess;
 }
 
+hipError_t launch_pp(const ConvArgs &a, dim3 grid, hipStream_t st)
+{
+    if (128 + 2 * a.W + 2 >= kPpRows || a.R != 3 || a.S != 3 || a.stride != 1 || a.pad != 1 || a.Cg % 64 != 0 ||
+        a.kr_per_split % (9 * 64) != 0)
+        return hipErrorInvalidValue;
+    if (a.ycl)
+        launch_kernel(igemm_bf16_pp_kernel<true>, grid, dim3(512), 0, st, a);
+    else
+        launch_kernel(igemm_bf16_pp_kernel<false>, grid, dim3(512), 0, st, a);
+    return hipSuccess;
+}
+
 void launch_dma(const ConvArgs &a, int tile, dim3 grid, hipStream_t st)
 {
     if (a.R == 1 && a.S == 1)
@@ -1639,6 +2004,39 @@ static NhwcPlan plan_dma(const ConvProblem &p, int num_cus, const void *x, int m
     else if (p.R == 3 && p.S == 3 && p.stride == 1 && p.pad == 1 && plan.tile == 1 && p.Cg == 64 &&
              splits == 1 && 128 + 2 * p.W + 2 <= 256)
         plan.halo = 256;
+    // 3x3 stride-1 layers whose 128 x 128 tiles fill one round of one
+    // work-group per CU go to igemm_bf16_pp_kernel: unsplit from half a round
+    // up (above one round its second round of full length loses: batch 64,
+    // 28x28 128 -> 128, 392 tiles: 25.7 -> 32.5 us), from 3/8 of a round with at
+    // most 48 chunks; otherwise long reductions split over whole channel blocks
+    // when that fills 3/4 of the round.  Calls measured, before -> with it
+    // (channel-last, filter pack included): 14x14 256 -> 256 at batch 64
+    // 37.4 -> 27.7 us, 32 27.7 -> 25.0, 80 35.8 -> 27.8; 14x14 128 -> 256 at batch
+    // 64 21.7 -> 19.1; 14x14 512 -> 512 at batch 32 67.1 -> 45.9; 7x7 512 -> 512
+    // at batch 128 65.7 -> 46.7, 64 (two parts) 40.7 -> 39.9, 48 (three) 37.6 ->
+    // 36.3.  Not from a quarter of a round (batch 24, 14x14 256: 27.6 -> 28.3
+    // with an fp32 y), nor unsplit below half with 72 chunks (40.8 -> 43.6).
+    if (p.R == 3 && p.S == 3 && p.stride == 1 && p.pad == 1 && p.Kg > 64 && chunks >= 18 &&
+        128 + 2 * p.W + 2 < kPpRows && wgs(0) <= num_cus) {
+        const int blocks = p.Cg / 64;
+        int parts = 0;
+        if (wgs(0) * 2 > num_cus || (wgs(0) * 8 >= 3L * num_cus && chunks <= 48)) {
+            parts = 1;
+        } else if (chunks >= 54) {
+            const int per = std::max(2, ceil_div(blocks, (int)(num_cus / wgs(0))));
+            const int n = ceil_div(blocks, per);
+            if (n <= max_splits && wgs(0) * n * 4 >= 3L * num_cus) parts = n;
+        }
+        if (parts) {
+            const int per = ceil_div(blocks, parts);
+            plan.pp = 1;
+            plan.tile = 0;
+            plan.halo = kPpRows;
+            plan.splits = parts;
+            plan.kr_per_split = per * 9 * 64;           // whole channel blocks
+            plan.partial_bytes = parts > 1 ? (size_t)parts * p.K * p.M * sizeof(float) : 0;
+        }
+    }
     const ConvProblem cp = copied_problem(p);
     plan.xcl_bytes = plan.nchwb || x_nhwc ? 0 : (size_t)cp.N * cp.C * cp.H * cp.W * sizeof(uint16_t);
     plan.copy_cb = plane_copy_block(p, num_cus);
@@ -1693,6 +2091,11 @@ void describe_nhwc_bf16(const ConvProblem &p, const NhwcPlan &plan, char *buf, i
     const bool copy = !plan.nchwb && !plan.x_nhwc;
     const char *variant = p.ycl ? "_cl" : p.res && plan.splits == 1 ? "_res" : "";
     const char *reduce = plan.splits == 1 ? "" : p.ycl ? " + splitk_reduce_cl_kernel" : " + splitk_reduce_kernel";
+    if (plan.dma && plan.pp) {
+        snprintf(buf, len, "%sigemm_bf16_pp_kernel<%s>%s", copy ? tname : "", p.ycl ? "true" : "false", reduce);
+        *launches = (copy ? 2 : 1) + (plan.splits > 1 ? 1 : 0);
+        return;
+    }
     if (plan.dma && plan.halo) {
         const TileD &d = kTilesD[plan.tile];
         snprintf(buf, len, "%sigemm_bf16_halo%s_kernel<%d, %d, 2, 2, %d, %d>%s", copy ? tname : "", variant,
@@ -1753,7 +2156,9 @@ hipError_t launch_nhwc_bf16(const ConvProblem &p, const NhwcPlan &plan, const ui
         const long wgs = (long)ceil_div(p.M, d.bpx) * ceil_div(p.Kg, d.bkc) * p.groups * plan.splits;
         if (hook && (e = hook->before_launch(hook->ctx, st)) != hipSuccess) return e;
         if (plan.halo) {
-            if ((e = launch_halo(a, d.bkc, plan.halo, dim3((unsigned)wgs), st)) != hipSuccess) return e;
+            e = plan.pp ? launch_pp(a, dim3((unsigned)wgs), st)
+                        : launch_halo(a, d.bkc, plan.halo, dim3((unsigned)wgs), st);
+            if (e != hipSuccess) return e;
         } else
             launch_dma(a, plan.tile, dim3((unsigned)wgs), st);
         if ((e = hipGetLastError()) != hipSuccess || plan.splits == 1) return e;
@@ -1813,7 +2218,9 @@ hipError_t launch_nhwc_bf16(const ConvProblem &p, const NhwcPlan &plan, const ui
         const TileD &d = kTilesD[plan.tile];
         const long wgs = (long)ceil_div(p.M, d.bpx) * ceil_div(p.Kg, d.bkc) * p.groups * plan.splits;
         if (plan.halo) {
-            if ((e = launch_halo(a, d.bkc, plan.halo, dim3((unsigned)wgs), st)) != hipSuccess) return e;
+            e = plan.pp ? launch_pp(a, dim3((unsigned)wgs), st)
+                        : launch_halo(a, d.bkc, plan.halo, dim3((unsigned)wgs), st);
+            if (e != hipSuccess) return e;
         } else
             launch_dma(a, plan.tile, dim3((unsigned)wgs), st);
         if ((e = hipGetLastError()) != hipSuccess || plan.splits == 1) return e;

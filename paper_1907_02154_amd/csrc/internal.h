@@ -218,6 +218,7 @@ struct NhwcPlan {
     int copy_cb;          // channels per work-group of the whole-plane copy
     int halo;             // 3x3 stride-1 layers: patch rows of the halo kernel (0: not used);
                           // its filters are packed in 64-channel blocks
+    int pp;               // (halo) the kernel of two alternating wavefront groups
     int x_nhwc;           // x is already channel-last: no copy
 };
 bool nhwc_bf16_eligible(const ConvProblem &p);
