@@ -404,12 +404,21 @@ hipError_t launch_pack(const Resolved &r, void *dst, hipStream_t st)
     return launch_pack_krsc(r.p, r.w, dst, elem, st, cblk);
 }
 
+bool packs_with_copy(const Resolved &r)
+{
+    return r.pack_per_call && r.impl == IMPL_NHWC_BF16 && nhwc_packs_with_copy(r.p, r.nplan);
+}
+
 hipError_t enqueue(const Resolved &r0, float *ws, hipStream_t st, const LaunchHook *hook)
 {
     Resolved r = r0;
     // workspace layout: [packed filters (per-call packing)][copy of x][split partials]
     char *cursor = reinterpret_cast<char *>(ws);
-    if (r.pack_per_call) {
+    const bool pack_late = packs_with_copy(r);
+    if (pack_late) {
+        r.wk = cursor;
+        cursor += round256(packed_bytes(r));
+    } else if (r.pack_per_call) {
         if (hook) {
             hipError_t e = hook->before_launch(hook->ctx, st);
             if (e != hipSuccess) return e;
@@ -433,7 +442,8 @@ hipError_t enqueue(const Resolved &r0, float *ws, hipStream_t st, const LaunchHo
     const void *wkern = r.wk ? r.wk : r.w;
     if (r.impl == IMPL_NHWC_BF16)
         return launch_nhwc_bf16(r.p, r.nplan, static_cast<const uint16_t *>(r.x),
-                                static_cast<const uint16_t *>(wkern), r.bias, r.y, xcl, ws, st, hook);
+                                static_cast<const uint16_t *>(wkern), r.bias, r.y, xcl, ws, st, hook,
+                                pack_late ? static_cast<const uint16_t *>(r.w) : nullptr);
     const float *xf = static_cast<const float *>(r.x), *wf = static_cast<const float *>(wkern);
     if (r.impl == IMPL_IGEMM) return launch_igemm_f32(r.p, r.plan, xf, wf, r.bias, r.y, ws, st, hook);
     if (r.impl == IMPL_WAVE) return launch_wave_f32(r.p, r.wplan, xf, wf, r.bias, r.y, ws, st, hook);
@@ -484,10 +494,11 @@ size_t workspace_bytes(const Resolved &r)
 
 void describe(const Resolved &r, char *buf, int len, int *launches)
 {
-    if (r.pack_per_call) {
+    if (r.pack_per_call && !packs_with_copy(r)) {
         const int n = r.wlayout == WL_STEM ? snprintf(buf, len, "pack_stem_kernel + ")
                       : r.wlayout == WL_WAVE ? snprintf(buf, len, "pack_wave_kernel + ")
                       : r.wlayout == WL_SPLIT3 ? snprintf(buf, len, "split3_pack_kernel + ")
+                      : r.kind == OP_DENSE_BF16 && pack_krsc_runs(r.p) ? snprintf(buf, len, "pack_krsc_run_kernel + ")
                                                : snprintf(buf, len, "pack_krsc_kernel<%s> + ",
                                      r.kind == OP_DENSE_BF16 ? "unsigned short" : "float");
         if (n > 0 && n < len) {
@@ -507,7 +518,7 @@ void describe_kernel(const Resolved &r, char *buf, int len, int *launches)
     case IMPL_WAVE: describe_wave_f32(r.p, r.wplan, buf, len, launches); break;
     case IMPL_SPLIT_F32: describe_split3(r.p, r.splan, buf, len, launches); break;
     case IMPL_IGEMM_BF16: describe_igemm_bf16(r.p, r.plan, r.bfast, r.bva, buf, len, launches); break;
-    case IMPL_NHWC_BF16: describe_nhwc_bf16(r.p, r.nplan, buf, len, launches); break;
+    case IMPL_NHWC_BF16: describe_nhwc_bf16(r.p, r.nplan, buf, len, launches, packs_with_copy(r)); break;
     case IMPL_STEM_BF16: describe_stem_bf16(buf, len, launches); break;
     case IMPL_POOL_NHWC:
         snprintf(buf, len, r.p.R == 3 && r.p.S == 3 ? "maxpool_nhwc_bf16_kernel<3, 3>" : "maxpool_nhwc_bf16_kernel<0, 0>");

@@ -14,7 +14,7 @@
 //     and stores y in NCHW fp32 with bias + activation.
 // Requirements: C/groups % KRC == 0 (every reduction chunk of KRC elements
 // is KRC channels at one filter position), so the chunk's (r, s) is uniform.
-#include "internal.h"
+#include "pack_krsc.h"
 
 #include <algorithm>
 #include <cstdio>
@@ -67,18 +67,17 @@ __device__ __forceinline__ void copy_tile_out(const NhwcCopyArgs &a, const uint1
     }
 }
 
+// tile: [channel][pixel]; channel row c is stored at row c ^ ((c >> 3) & 7),
+// so the transposed reads (8 lanes on channel rows 8*o + e, o = 0..7) fall in
+// 8 distinct bank groups.
 template <int RV>
-__global__ __launch_bounds__(256) void nchw_to_nhwc_bf16_kernel(NhwcCopyArgs a)
+__device__ __forceinline__ void copy_tiles(const NhwcCopyArgs &a, int block, uint16_t (*tile)[64 + 8])
 {
     constexpr int PX = 64;
-    // [channel][pixel]; channel row c is stored at row c ^ ((c >> 3) & 7), so
-    // the transposed reads (8 lanes on channel rows 8*o + e, o = 0..7) fall in
-    // 8 distinct bank groups
-    __shared__ __attribute__((aligned(16))) uint16_t tile[64][PX + 8];
     auto row = [](int c) { return c ^ ((c >> 3) & 7); };
     const int t = threadIdx.x;
-    const int c0 = (blockIdx.x % a.tiles_c) * 64;
-    const int p0 = (blockIdx.x / a.tiles_c) * PX;
+    const int c0 = (block % a.tiles_c) * 64;
+    const int p0 = (block / a.tiles_c) * PX;
     if constexpr (RV > 1) {
         constexpr int GR = PX / RV;                 // pixel groups per channel row
 #pragma unroll
@@ -117,6 +116,13 @@ __global__ __launch_bounds__(256) void nchw_to_nhwc_bf16_kernel(NhwcCopyArgs a)
     }
     __syncthreads();
     copy_tile_out(a, tile, c0, p0, t);
+}
+
+template <int RV>
+__global__ __launch_bounds__(256) void nchw_to_nhwc_bf16_kernel(NhwcCopyArgs a)
+{
+    __shared__ __attribute__((aligned(16))) uint16_t tile[64][64 + 8];
+    copy_tiles<RV>(a, blockIdx.x, tile);
 }
 
 // Stride-2 subsampling copy (1x1 stride-2 layers) reading G sampled pixels
@@ -170,12 +176,11 @@ __global__ __launch_bounds__(256) void nchw_to_nhwc_sampled_bf16_kernel(NhwcCopy
 // 16-byte store.  Requires C % 8 == 0 and a 16-byte aligned x.
 constexpr int kPlaneElems = 16384;    // 32 KB of LDS
 
-__global__ __launch_bounds__(256) void nchw_to_nhwc_plane_bf16_kernel(NhwcCopyArgs a)
+__device__ __forceinline__ void copy_plane(const NhwcCopyArgs &a, int block, uint16_t *plane)
 {
-    __shared__ __attribute__((aligned(16))) uint16_t plane[kPlaneElems];
     const int t = threadIdx.x;
-    const int n = blockIdx.x / a.tiles_c;
-    const int c0 = (blockIdx.x % a.tiles_c) * a.cb;
+    const int n = block / a.tiles_c;
+    const int c0 = (block % a.tiles_c) * a.cb;
     const int cn = min(a.cb, a.C - c0);                // a multiple of 8
     const uint4 *src = reinterpret_cast<const uint4 *>(a.x + ((long)n * a.C + c0) * a.HW);
     const int units = cn * a.HW / 8;
@@ -195,6 +200,31 @@ __global__ __launch_bounds__(256) void nchw_to_nhwc_plane_bf16_kernel(NhwcCopyAr
             d[e] = (uint32_t)col[2 * e * a.HW] | ((uint32_t)col[(2 * e + 1) * a.HW] << 16);
         *reinterpret_cast<uint4 *>(out + (long)pq * a.C + 8 * o) = make_uint4(d[0], d[1], d[2], d[3]);
     }
+}
+
+__global__ __launch_bounds__(256) void nchw_to_nhwc_plane_bf16_kernel(NhwcCopyArgs a)
+{
+    __shared__ __attribute__((aligned(16))) uint16_t plane[kPlaneElems];
+    copy_plane(a, blockIdx.x, plane);
+}
+
+// A call's filter packing and copy in one launch: the first work-groups pack,
+// the others copy (RV as in nchw_to_nhwc_bf16_kernel, 0 the whole-plane copy).
+// Neither fills the chip for long, and the conv waits for both: 256 -> 256 3x3
+// filters and a 6.4 MB x took 10 us as two launches (gathering pack), 5.1 us as
+// one; the 3x3 layer of 14x14 planes at batch 64 32.2 -> 27.5 us a call.
+template <int RV>
+__global__ __launch_bounds__(256) void pack_nchw_to_nhwc_bf16_kernel(PackRuns p, NhwcCopyArgs a)
+{
+    constexpr int COPY = RV == 0 ? kPlaneElems : 64 * (64 + 8);
+    __shared__ __attribute__((aligned(16))) uint16_t smem[COPY > 4 * kPackTile ? COPY : 4 * kPackTile];
+    const int copy = (int)blockIdx.x - p.blocks;
+    if (copy < 0)
+        pack_krsc_run(p, blockIdx.x, smem);
+    else if constexpr (RV == 0)
+        copy_plane(a, copy, smem);
+    else
+        copy_tiles<RV>(a, copy, reinterpret_cast<uint16_t(*)[64 + 8]>(smem));
 }
 
 // MFMA roles: the pixel tile is the MFMA's A operand (rows i) and the filter
@@ -2010,7 +2040,8 @@ static NhwcPlan plan_dma(const ConvProblem &p, int num_cus, const void *x, int m
     // 28x28 128 -> 128, 392 tiles: 25.7 -> 32.5 us), from 3/8 of a round with at
     // most 48 chunks; otherwise long reductions split over whole channel blocks
     // when that fills 3/4 of the round.  Calls measured, before -> with it
-    // (channel-last, filter pack included): 14x14 256 -> 256 at batch 64
+    // (channel-last, with a filter pack 1 us, at 512 channels 7 us slower than
+    // today's on both sides): 14x14 256 -> 256 at batch 64
     // 37.4 -> 27.7 us, 32 27.7 -> 25.0, 80 35.8 -> 27.8; 14x14 128 -> 256 at batch
     // 64 21.7 -> 19.1; 14x14 512 -> 512 at batch 32 67.1 -> 45.9; 7x7 512 -> 512
     // at batch 128 65.7 -> 46.7, 64 (two parts) 40.7 -> 39.9, 48 (three) 37.6 ->
@@ -2075,14 +2106,23 @@ NhwcPlan plan_nhwc_bf16(const ConvProblem &p, int num_cus, const void *x, int ma
     return plan;
 }
 
+// Packed filters of one tap are the filters as given, and a copy that samples
+// x is of a 1x1 layer.
+bool nhwc_packs_with_copy(const ConvProblem &p, const NhwcPlan &plan)
+{
+    return p.R * p.S > 1 && !plan.nchwb && !plan.x_nhwc && pack_krsc_runs(p);
+}
+
 void describe_nhwc_bf16(const ConvProblem &p, const NhwcPlan &plan, char *buf, int len,
-                        int *launches)
+                        int *launches, bool pack_with_copy)
 {
     int R = rs_template(p.R), S = rs_template(p.S);
     if (R != S) R = S = 0;
     char tname[64];
     const int rv = copy_read_width(p, nullptr);
-    if (rv == 0)
+    if (pack_with_copy)
+        snprintf(tname, sizeof tname, "pack_nchw_to_nhwc_bf16_kernel<%d> + ", rv);
+    else if (rv == 0)
         snprintf(tname, sizeof tname, "nchw_to_nhwc_plane_bf16_kernel + ");
     else if (rv < 0)
         snprintf(tname, sizeof tname, "nchw_to_nhwc_sampled_bf16_kernel<%d> + ", -rv);
@@ -2121,9 +2161,10 @@ void describe_nhwc_bf16(const ConvProblem &p, const NhwcPlan &plan, char *buf, i
 
 hipError_t launch_nhwc_bf16(const ConvProblem &p, const NhwcPlan &plan, const uint16_t *x,
                             const uint16_t *w_krsc, const float *bias, float *y, uint16_t *xcl,
-                            float *partials, hipStream_t st, const LaunchHook *hook)
+                            float *partials, hipStream_t st, const LaunchHook *hook, const uint16_t *w_kcrs)
 {
     hipError_t e = hipSuccess;
+    if (w_kcrs && !nhwc_packs_with_copy(p, plan)) return hipErrorInvalidValue;
     if (plan.dma && plan.nchwb) {
         ConvArgs a = make_args(p);
         a.x = x;
@@ -2185,14 +2226,32 @@ hipError_t launch_nhwc_bf16(const ConvProblem &p, const NhwcPlan &plan, const ui
     ca.dv_pq = make_fastdiv(ca.PQ);
     ca.dv_q = make_fastdiv(ca.Q);
     const int rv = copy_read_width(p, x);
-    const dim3 tg((unsigned)((long)ceil_div(ca.npq, 64) * ca.tiles_c)), tb(256);
+    long blocks = (long)ceil_div(ca.npq, 64) * ca.tiles_c;
     if (rv == 0) {
         // the block must fit the kernel's LDS buffer (32 * H*W always does here)
         ca.cb = plan.copy_cb >= 8 ? plan.copy_cb : 64;
         while (ca.cb > 8 && ca.cb * ca.HW > kPlaneElems) ca.cb /= 2;
         ca.tiles_c = ceil_div(p.C, ca.cb);
-        launch_kernel(nchw_to_nhwc_plane_bf16_kernel, dim3((unsigned)((long)p.N * ca.tiles_c)), tb, 0, st, ca);
+        blocks = (long)p.N * ca.tiles_c;
     }
+    const dim3 tg((unsigned)blocks), tb(256);
+    if (w_kcrs) {
+        // the kernel reads these filters, packed
+        const PackRuns pr = make_pack_runs(p, w_kcrs, const_cast<uint16_t *>(w_krsc), plan.halo ? 64 : 0);
+        const dim3 pg((unsigned)(blocks + pr.blocks));
+        if (rv == 0)
+            launch_kernel(pack_nchw_to_nhwc_bf16_kernel<0>, pg, tb, 0, st, pr, ca);
+        else if (rv == 8)
+            launch_kernel(pack_nchw_to_nhwc_bf16_kernel<8>, pg, tb, 0, st, pr, ca);
+        else if (rv == 4)
+            launch_kernel(pack_nchw_to_nhwc_bf16_kernel<4>, pg, tb, 0, st, pr, ca);
+        else if (rv == 1)
+            launch_kernel(pack_nchw_to_nhwc_bf16_kernel<1>, pg, tb, 0, st, pr, ca);
+        else
+            return hipErrorInvalidValue;
+    }
+    else if (rv == 0)
+        launch_kernel(nchw_to_nhwc_plane_bf16_kernel, tg, tb, 0, st, ca);
     else if (rv == 8)
         launch_kernel(nchw_to_nhwc_bf16_kernel<8>, tg, tb, 0, st, ca);
     else if (rv == 4)

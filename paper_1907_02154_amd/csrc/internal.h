@@ -224,11 +224,15 @@ struct NhwcPlan {
 bool nhwc_bf16_eligible(const ConvProblem &p);
 // x_nhwc: x is given channel-last (direct-to-LDS kernels only, C/groups % 64 == 0).
 NhwcPlan plan_nhwc_bf16(const ConvProblem &p, int num_cus, const void *x, int max_splits, bool x_nhwc = false);
+// Whether one launch packs the filters of a call and copies its x channel-last;
+// launch_nhwc_bf16 then takes the filters as given (w_kcrs) and where to pack them.
+bool nhwc_packs_with_copy(const ConvProblem &p, const NhwcPlan &plan);
 hipError_t launch_nhwc_bf16(const ConvProblem &p, const NhwcPlan &plan, const uint16_t *x,
                             const uint16_t *w_krsc, const float *bias, float *y, uint16_t *xcl,
-                            float *partials, hipStream_t st, const LaunchHook *hook = nullptr);
+                            float *partials, hipStream_t st, const LaunchHook *hook = nullptr,
+                            const uint16_t *w_kcrs = nullptr);
 void describe_nhwc_bf16(const ConvProblem &p, const NhwcPlan &plan, char *buf, int len,
-                        int *launches);
+                        int *launches, bool pack_with_copy);
 
 // bf16 7x7/2 stem on <= 4 channels with 112 output columns (filters packed by
 // launch_pack_stem into [K][28 tap pairs][8]).
@@ -347,6 +351,9 @@ int wave_order(const ConvProblem &p);
 int wave_kred(const ConvProblem &p);
 size_t wave_packed_floats(const ConvProblem &p);
 hipError_t launch_pack_wave(const ConvProblem &p, const float *w, float *packed, hipStream_t st);
+// Whether a bf16 layer's filters are packed by whole runs of channels
+// (pack_krsc.h) rather than one value at a time.
+bool pack_krsc_runs(const ConvProblem &p);
 // cblk: channel block of the (block, r, s, c) order; 0 = C/groups (plain KRSC).
 hipError_t launch_pack_krsc(const ConvProblem &p, const void *w, void *packed, size_t elem,
                             hipStream_t st, int cblk = 0);

@@ -6,9 +6,11 @@
 // With the reduction ordered (r, s, c), c innermost, any 8 consecutive
 // reduction indices (Cg % 8 == 0) are 8 channels at one filter tap: a conv
 // kernel checks the padding and forms the input address once per 8 taps
-// instead of once per tap.  Lanes walk the destination, so stores are
-// contiguous; the reads gather within one filter's Cg*R*S block (L2-resident).
-#include "internal.h"
+// instead of once per tap.  bf16 filters of up to 5x5 taps with Cg % 8 == 0 go
+// through LDS (pack_krsc.h); for the rest lanes walk the destination, so
+// stores are contiguous, and the reads gather within one filter's Cg*R*S
+// block (L2-resident).
+#include "pack_krsc.h"
 
 namespace miconv {
 namespace {
@@ -27,6 +29,12 @@ __global__ __launch_bounds__(256) void pack_krsc_kernel(const T *__restrict__ sr
         const int c = cb * cblk + (rem2 - rs * cblk);
         dst[i] = src[(k * Cg + c) * RS + rs];
     }
+}
+
+__global__ __launch_bounds__(256) void pack_krsc_run_kernel(PackRuns a)
+{
+    __shared__ __attribute__((aligned(16))) uint16_t tile[4 * kPackTile];
+    pack_krsc_run(a, blockIdx.x, tile);
 }
 
 // Wave-kernel order: one slot per (group, 32-filter block kb, 8-tap block b,
@@ -79,6 +87,11 @@ int wave_order(const ConvProblem &p)
 
 int wave_kred(const ConvProblem &p) { return wave_order(p) == 2 ? 4 * p.R * p.S : p.Kred; }
 
+bool pack_krsc_runs(const ConvProblem &p)
+{
+    return p.Cg % 8 == 0 && p.R * p.S <= kPackRS && (long)p.K * ceil_div(p.Cg, 64) < (1L << 31) - 4;
+}
+
 size_t wave_packed_floats(const ConvProblem &p)
 {
     return (size_t)p.groups * ceil_div(p.Kg, 32) * ceil_div(wave_kred(p), 8) * 256;
@@ -100,6 +113,12 @@ hipError_t launch_pack_krsc(const ConvProblem &p, const void *w, void *packed, s
     const long total = (long)p.K * p.Cg * p.R * p.S;
     if (cblk <= 0) cblk = p.Cg;
     if (p.Cg % cblk != 0) return hipErrorInvalidValue;
+    if (elem == sizeof(uint16_t) && pack_krsc_runs(p)) {
+        if ((uintptr_t)packed % 16 != 0) return hipErrorInvalidValue;   // every caller's packed filters are
+        const PackRuns r = make_pack_runs(p, static_cast<const uint16_t *>(w), static_cast<uint16_t *>(packed), cblk);
+        launch_kernel(pack_krsc_run_kernel, dim3((unsigned)r.blocks), dim3(256), 0, st, r);
+        return hipGetLastError();
+    }
     long blocks = (total + 255) / 256;
     if (blocks > 65536) blocks = 65536;
     if (elem == sizeof(float))

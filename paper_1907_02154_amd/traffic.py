@@ -63,6 +63,8 @@ SOURCES = {
     "dw_generic_kernel": "dwconv.hip",
     "conv_direct_kernel": "conv_direct.hip",
     "pack_krsc_kernel": "pack.hip",
+    "pack_krsc_run_kernel": "pack.hip",
+    "pack_nchw_to_nhwc_bf16_kernel": "conv_nhwc_bf16.hip",
     "pack_wave_kernel": "pack.hip",
     "stem7_bf16_kernel": "conv_stem_bf16.hip",
     "pack_stem_kernel": "conv_stem_bf16.hip",
