@@ -84,7 +84,7 @@ __device__ __forceinline__ void wave_body(const ConvArgs &a)
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
-    const int wave = tid >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int h = lane >> 5, ll = lane & 31;
     // XCD-aware tile order: the hardware deals work-groups to the 8 XCDs
     // round-robin (work-group b runs on XCD b % 8), so logical tiles are
@@ -98,7 +98,7 @@ __device__ __forceinline__ void wave_body(const ConvArgs &a)
     // work-group) and runs its whole reduction: for short reductions over
     // many tiles, where splitting 8-tap blocks across wavefronts would leave
     // most of them idle and add an LDS combine per tile.
-    const unsigned L = IND ? LW * WAVES + (threadIdx.x >> 6) : LW;
+    const unsigned L = IND ? LW * WAVES + wave : LW;
     if (IND && L >= (unsigned)(ceil_div(a.M, 32 * BJ) * ceil_div(a.Kg, 32) * a.groups)) return;
     const unsigned t1 = fdiv(L, a.dv_mt);
     const unsigned mx = L - t1 * mtiles;
@@ -155,9 +155,46 @@ __device__ __forceinline__ void wave_body(const ConvArgs &a)
         drr = kStep - drq * cb;
     }
 
+    // (c, r, s) order: a wavefront's next 16 blocks' taps, as 4 * (offset from
+    // the pixel's first tap) and the number of the filter position, in its own
+    // part of LDS: each lane decodes two taps, so a block costs a lane 24
+    // instructions.  (Each lane decoding its own four taps, two divisions and
+    // three products each, held the matrix cores up: 3x3 stride 2, 100 -> 120
+    // channels on 55x57 at batch 5 23.4 -> 17.9 us a call.)
+    constexpr bool kTable = ORD == 0 && !(R_ == 1 && S_ == 1);
+    constexpr int kTapPast = 31;              // a filter position no pixel has
+    __shared__ __attribute__((aligned(16))) unsigned tab_off[kTable ? WAVES : 1][kTable ? 128 : 1];
+    __shared__ __attribute__((aligned(16))) uint8_t tab_pos[kTable ? WAVES : 1][kTable ? 128 : 1];
+    const bool table = kTable && ((R_ && S_) || RS <= kTapPast);
+    unsigned inside[BJ], xpix[BJ];            // filter positions inside the image, one bit each; first tap
+    if constexpr (kTable) {
+#pragma unroll
+        for (int j = 0; j < BJ; ++j) {
+            xpix[j] = 4u * (xoff[j] + (unsigned)(ih0[j] * a.W + iw0[j]));
+            inside[j] = 0;
+            unsigned cols = 0;
+            for (int s = 0; s < S && table; ++s) cols |= (unsigned)((unsigned)(iw0[j] + s) < (unsigned)a.W) << s;
+            for (int r = 0; r < R && table; ++r)
+                inside[j] |= mvalid[j] && (unsigned)(ih0[j] + r) < (unsigned)a.H ? cols << (r * S) : 0u;
+        }
+    }
+    auto fill_table = [&](int first, int step) {   // of blocks first, first + step, ...
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int t = lane + 64 * i;
+            const int kr = kr_begin + 8 * (first + (t >> 3) * step) + (t & 7);
+            const int c = kr / RS;
+            const int rs = kr - c * RS;
+            const int r = rs / S;
+            tab_off[wave][t] = 4u * ((unsigned)c * a.HW + (unsigned)(r * a.W + rs - r * S));
+            tab_pos[wave][t] = (uint8_t)(kr < kr_end ? rs : kTapPast);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    };
+
     // Block blk (< nblk) of this split: taps kr_begin + 8*blk + 4h + e,
     // e = 0..3.  Called for the wavefront's blocks in increasing order.
-    auto load = [&](Frag &f, int blk) {
+    auto load = [&](Frag &f, int blk, int i) {   // i: the block's number among the wavefront's
         const int kr0 = kr_begin + 8 * blk + 4 * h;
         typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
         if constexpr (KC == 0) {
@@ -248,6 +285,21 @@ __device__ __forceinline__ void wave_body(const ConvArgs &a)
                     f.bv[j][e] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(xres, off, 0, 0));
                 }
             }
+        } else if (table) {
+            if ((i & 15) == 0) fill_table(blk, IND ? 1 : WAVES);
+            const int t = 8 * (i & 15) + 4 * h;
+            const uint4 to = *reinterpret_cast<const uint4 *>(&tab_off[wave][t]);
+            const unsigned off4[4] = {to.x, to.y, to.z, to.w};
+            const unsigned pos4 = *reinterpret_cast<const unsigned *>(&tab_pos[wave][t]);
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int j = 0; j < BJ; ++j) {
+                    const bool ok = (inside[j] >> ((pos4 >> (8 * e)) & 31)) & 1;
+                    f.bv[j][e] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(
+                        xres, select_offset(ok, xpix[j] + off4[e], kOut), 0, 0));
+                }
+            if ((i & 15) == 15) __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         } else {
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
@@ -309,7 +361,7 @@ __device__ __forceinline__ void wave_body(const ConvArgs &a)
                     for (int j = 0; j < BJ; ++j)
                         acc[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(f[d].av[e], f[d].bv[j][e], acc[j], 0, 0, 0);
             }
-            if (it + d < my_blocks) load(f[d], IND ? it + d : wave + (it + d) * WAVES);
+            if (it + d < my_blocks) load(f[d], IND ? it + d : wave + (it + d) * WAVES, it + d);
         }
     }
 
