@@ -840,7 +840,7 @@ def vision_record(steps: int, cpu_seconds: float) -> dict:
     ms = _graph_ms(torch, fn, 2 * max(steps // 10, 2), stream)
     gbs = 8.0 * n / (ms * 1e-3) / 1e9
     rec["scan"] = {"n": n, "us": round(ms * 1e3, 1), "GBs_algorithmic": round(gbs, 1), "buffer_sets": 2}
-    rec["roofline"] = {"kernel": "scan (upsweep + tile sums + downsweep)", "bound": "hbm",
+    rec["roofline"] = {"kernel": "scan (upsweep + downsweep)", "bound": "hbm",
                        "achieved": round(gbs, 1), "peak": PEAK_HBM_GBS, "unit": "GB/s",
                        "frac": round(gbs / PEAK_HBM_GBS, 4), "traffic": None}
     if cpu_seconds > 0:

@@ -42,8 +42,8 @@ extern "C" {
  * the block totals, down-sweep (each block adds the scanned total of the
  * blocks before it).  Many rows, or short ones, take one work-group per row
  * (the stages inside the work-group, no synchronisation across
- * work-groups); a few long rows take the stages across work-groups, one
- * launch each, with the tile totals in the workspace.
+ * work-groups); a few long rows take them across work-groups, in two
+ * launches, with the sums of about 1024 chunks in the workspace.
  * Errors: MICONV_ERR_NULL (x or y NULL), MICONV_ERR_SHAPE (rows < 1,
  * n < 1), MICONV_ERR_TOO_LARGE (rows * n >= 2^31), MICONV_ERR_WORKSPACE. */
 long vision_scan_workspace_bytes(int rows, long n);

@@ -27,10 +27,6 @@ constexpr int kScanItems = 16;                        // values per thread (regi
 constexpr int kScanTile = kScanThreads * kScanItems;  // 4096 values per tile
 constexpr int kScanWide = 1024;                       // a work-group owning one of few rows
 
-// One spare LDS word per 16: thread t's values t*16 .. t*16+15 start in
-// distinct banks.
-__device__ __forceinline__ int pad16(int i) { return i + (i >> 4); }
-
 // Hillis-Steele inclusive scan of one value per thread over a work-group of
 // NT threads: in pass d every thread adds the value held by the thread 2^d
 // before it.  Within a wavefront the passes are lane shuffles; the NT/64
@@ -64,196 +60,256 @@ __device__ int wg_scan_incl(int v, int *wsum, int *total)
     return r;
 }
 
-// The scanned values: an int32 array, four values per 16-byte load where aligned.
-struct SrcI32 {
-    const int32_t *x;
-    __device__ int operator()(long i) const { return x[i]; }
-    __device__ bool aligned(long i) const { return (((uintptr_t)(x + i)) & 15) == 0; }
-    __device__ int4 vec(long i) const { return *reinterpret_cast<const int4 *>(x + i); }
-};
-
-// The three stages on one tile [base, base + len) (len <= NT * kScanItems),
-// carry = sum of everything before the tile.  Up-sweep: thread t scans its
-// kScanItems consecutive values sequentially in registers; scan: Hillis-
-// Steele over the thread totals; down-sweep: each value gets the scanned
-// total of the threads before its own.  Loads and stores are striped over
-// the threads (coalesced) and transposed through LDS; NTS: whole tiles are
-// stored non-temporally.  Returns carry + the tile's sum.
-template <int NT, class Src, bool NTS = false>
-__device__ int scan_tile(const Src &src, long base, int len, int32_t *y, int carry, bool exclusive, int *tile,
-                         int *wsum)
+// Lane l gets the sum of lanes 0..l of its wavefront (every lane active):
+// Hillis-Steele passes within rows of 16 lanes, then the row totals
+// broadcast, all as DPP operands of the adds (no LDS).
+__device__ __forceinline__ int wave_scan_incl(int v)
 {
-    const int t = threadIdx.x;
-    if (len == NT * kScanItems && src.aligned(base)) {
-        // whole aligned tile: 16-byte loads, four values each (a group of
-        // four never straddles a pad word)
-#pragma unroll
-        for (int j = 0; j < kScanItems / 4; ++j) {
-            const int i4 = j * NT + t;
-            const int4 q = src.vec(base + 4L * i4);
-            const int o = pad16(4 * i4);
-            tile[o] = q.x;
-            tile[o + 1] = q.y;
-            tile[o + 2] = q.z;
-            tile[o + 3] = q.w;
-        }
-    } else {
-#pragma unroll
-        for (int j = 0; j < kScanItems; ++j) {
-            const int i = j * NT + t;
-            tile[pad16(i)] = i < len ? src(base + i) : 0;
-        }
-    }
-    __syncthreads();
-    int x0[kScanItems], v[kScanItems];
-    int run = 0;
-#pragma unroll
-    for (int k = 0; k < kScanItems; ++k) {
-        x0[k] = tile[pad16(t * kScanItems + k)];
-        run += x0[k];
-        v[k] = run;
-    }
-    int total;
-    const int incl = wg_scan_incl<NT>(run, wsum, &total);
-    const int before = incl - run + carry;
-#pragma unroll
-    for (int k = 0; k < kScanItems; ++k)
-        tile[pad16(t * kScanItems + k)] = before + (exclusive ? v[k] - x0[k] : v[k]);
-    __syncthreads();
-    if (len == NT * kScanItems && (((uintptr_t)(y + base)) & 15) == 0) {
-#pragma unroll
-        for (int j = 0; j < kScanItems / 4; ++j) {
-            const int i4 = j * NT + t;
-            const int o = pad16(4 * i4);
-            typedef int i32x4 __attribute__((ext_vector_type(4)));
-            const i32x4 q = {tile[o], tile[o + 1], tile[o + 2], tile[o + 3]};
-            if constexpr (NTS)
-                __builtin_nontemporal_store(q, reinterpret_cast<i32x4 *>(y + base + 4L * i4));
-            else
-                *reinterpret_cast<i32x4 *>(y + base + 4L * i4) = q;
-        }
-    } else {
-#pragma unroll
-        for (int j = 0; j < kScanItems; ++j) {
-            const int i = j * NT + t;
-            if (i < len) y[base + i] = tile[pad16(i)];
-        }
-    }
-    __syncthreads();   // the tile buffer is free
-    return carry + total;
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);   // row_shr:1
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);   // row_shr:2
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);   // row_shr:4
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);   // row_shr:8
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);   // row_bcast:15 into rows 1, 3
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);   // row_bcast:31 into rows 2, 3
+    return v;
 }
 
-// One work-group per row, its tiles in order with a running carry: the three
-// stages inside the work-group, nothing shared across work-groups.  Row r is
-// elements [r*n, r*n + n).  row_totals[r] (if given) gets the row's sum.
-// NT = 1024 when the rows are few (a tile of 16384 values per round trip).
-template <int NT, class Src>
-__global__ __launch_bounds__(NT) void scan_rows_kernel(Src src, long n, int32_t *y, int exclusive,
+// A tile of NT * kScanItems values in registers.  A wavefront owns 1024
+// consecutive values in four groups of 256; a lane holds four consecutive
+// values of each group, so that loads and stores are 16 bytes per lane and
+// contiguous over the wavefront as they stand: no pass through LDS.  Global
+// 16-byte accesses need 4-byte alignment only, which an int32 array has.
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+typedef i32x4 i32x4_dw __attribute__((aligned(4)));
+constexpr int kScanGroups = kScanItems / 4;
+
+__device__ __forceinline__ int scan_pos(int j)
+{
+    return (int)((threadIdx.x >> 6) * (64 * kScanItems) + j * 256 + 4 * (threadIdx.x & 63));
+}
+
+// The first len values at x; the rest of the tile is zero.
+template <int NT>
+__device__ __forceinline__ void scan_load(const int32_t *x, long len, i32x4 (&q)[kScanGroups])
+{
+    if (len >= NT * kScanItems) {
+#pragma unroll
+        for (int j = 0; j < kScanGroups; ++j) q[j] = *reinterpret_cast<const i32x4_dw *>(x + scan_pos(j));
+        return;
+    }
+    // the buffer's range check makes what lies past len zero, without branches
+    const __amdgpu_buffer_rsrc_t r =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t *>(x), (short)0, (int)len * 4, 0x00020000);
+#pragma unroll
+    for (int j = 0; j < kScanGroups; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            q[j][e] = (int)__builtin_amdgcn_raw_buffer_load_b32(r, (scan_pos(j) + e) * 4, 0, 0);
+}
+
+// What the values of this lane's groups are preceded by within the tile, and
+// the tile's sum.  wsum: NT/64 words no wavefront still reads (one barrier).
+template <int NT>
+__device__ __forceinline__ int scan_before(const i32x4 (&q)[kScanGroups], int (&before)[kScanGroups], int *wsum)
+{
+    constexpr int NW = NT / 64;
+    const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    int run = 0;
+#pragma unroll
+    for (int j = 0; j < kScanGroups; ++j) {
+        const int s = q[j][0] + q[j][1] + q[j][2] + q[j][3];
+        const int incl = wave_scan_incl(s);
+        before[j] = run + incl - s;
+        run += __builtin_amdgcn_readlane(incl, 63);
+    }
+    if (lane == 0) wsum[wid] = run;
+    __syncthreads();
+    const int incl = wave_scan_incl(lane < NW ? wsum[lane] : 0);
+    const int pre = __builtin_amdgcn_readlane(incl, wid) - run;
+#pragma unroll
+    for (int j = 0; j < kScanGroups; ++j) before[j] += pre;
+    return __builtin_amdgcn_readlane(incl, NW - 1);
+}
+
+// Stores the first len scanned values of a tile; NTS: whole tiles are stored
+// non-temporally.
+template <int NT, bool NTS>
+__device__ __forceinline__ void scan_store(int32_t *y, long len, i32x4 (&q)[kScanGroups],
+                                           const int (&before)[kScanGroups], int carry, bool exclusive)
+{
+#pragma unroll
+    for (int j = 0; j < kScanGroups; ++j) {
+        const int b = carry + before[j];
+        const int s0 = b + q[j][0], s1 = s0 + q[j][1], s2 = s1 + q[j][2], s3 = s2 + q[j][3];
+        q[j] = exclusive ? i32x4{b, s0, s1, s2} : i32x4{s0, s1, s2, s3};
+    }
+    if (len >= NT * kScanItems) {
+#pragma unroll
+        for (int j = 0; j < kScanGroups; ++j) {
+            if constexpr (NTS)
+                __builtin_nontemporal_store(q[j], reinterpret_cast<i32x4_dw *>(y + scan_pos(j)));
+            else
+                *reinterpret_cast<i32x4_dw *>(y + scan_pos(j)) = q[j];
+        }
+        return;
+    }
+    const int m = (int)len;
+#pragma unroll
+    for (int j = 0; j < kScanGroups; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (scan_pos(j) + e < m) y[scan_pos(j) + e] = q[j][e];
+}
+
+// One work-group per row, its tiles in order with a running carry, the next
+// tile's loads in flight meanwhile: the three stages inside the work-group,
+// nothing shared across work-groups.  Row r is elements [r*n, r*n + n).
+// row_totals[r] (if given) gets the row's sum.  NT = 1024 when the rows are
+// few (a tile of 16384 values per round trip).
+template <int NT>
+__global__ __launch_bounds__(NT) void scan_rows_kernel(const int32_t *x, long n, int32_t *y, int exclusive,
                                                        int32_t *row_totals)
 {
     constexpr int TILE = NT * kScanItems;
-    __shared__ int tile[TILE + TILE / 16];
-    __shared__ int wsum[NT / 64];
-    const long row = blockIdx.x;
+    __shared__ int wsum[2][NT / 64];
+    x += (long)blockIdx.x * n;
+    y += (long)blockIdx.x * n;
     int carry = 0;
-    for (long b = 0; b < n; b += TILE)
-        carry = scan_tile<NT>(src, row * n + b, (int)(n - b < TILE ? n - b : TILE), y, carry, exclusive != 0,
-                              tile, wsum);
-    if (row_totals && threadIdx.x == 0) row_totals[row] = carry;
+    long b = 0;
+    i32x4 q0[kScanGroups], q1[kScanGroups];
+    auto step = [&](i32x4 (&q)[kScanGroups], int *ws) {
+        int before[kScanGroups];
+        const int total = scan_before<NT>(q, before, ws);
+        scan_store<NT, false>(y + b, n - b, q, before, carry, exclusive != 0);
+        carry += total;
+        b += TILE;
+    };
+    scan_load<NT>(x, n, q0);
+    while (true) {
+        if (b + TILE >= n) {
+            step(q0, wsum[0]);
+            break;
+        }
+        scan_load<NT>(x + b + TILE, n - b - TILE, q1);
+        step(q0, wsum[0]);
+        if (b + TILE >= n) {
+            step(q1, wsum[1]);
+            break;
+        }
+        scan_load<NT>(x + b + TILE, n - b - TILE, q0);
+        step(q1, wsum[1]);
+    }
+    if (row_totals && threadIdx.x == 0) row_totals[blockIdx.x] = carry;
 }
 
-// The stages across work-groups (a few long rows).  Up-sweep: the sum of
-// every tile (grid: tiles x rows).
-template <class Src>
-__global__ __launch_bounds__(kScanThreads) void scan_upsweep_kernel(Src src, long n, int32_t *tile_sums)
+// The stages across work-groups (a few long rows), two launches bound by HBM:
+// 2^26 values 123.5 us, 4.35 TB/s of the 8 bytes per value it cannot do
+// without (three launches over tiles transposed through LDS: 128.0); 4 rows of
+// 16000001, unaligned, 181.7 -> 119.1 us; up to 4 million values, where the
+// launches count, 14.5 -> 11.9.  Up-sweep: the sum of every chunk of `chunk`
+// values, whole tiles (grid: chunks x rows).
+__global__ __launch_bounds__(kScanThreads) void scan_upsweep_kernel(const int32_t *x, long n, long chunk, int32_t *sums)
 {
     __shared__ int wsum[kScanThreads / 64];
-    const long base = (long)blockIdx.y * n + (long)blockIdx.x * kScanTile;
-    const long rem = n - (long)blockIdx.x * kScanTile;
-    const int len = (int)(rem < kScanTile ? rem : kScanTile);
+    const long c0 = (long)blockIdx.x * chunk;
+    const long len = n - c0 < chunk ? n - c0 : chunk;
+    x += (long)blockIdx.y * n + c0;
     int s = 0;
-    if (len == kScanTile && src.aligned(base)) {
+#pragma unroll 2
+    for (long b = 0; b < len; b += kScanTile) {
+        i32x4 q[kScanGroups];
+        scan_load<kScanThreads>(x + b, len - b, q);
 #pragma unroll
-        for (int j = 0; j < kScanItems / 4; ++j) {
-            const int4 q = src.vec(base + 4L * (j * kScanThreads + threadIdx.x));
-            s += q.x + q.y + q.z + q.w;
-        }
-    } else {
-#pragma unroll
-        for (int j = 0; j < kScanItems; ++j) {
-            const int i = j * kScanThreads + threadIdx.x;
-            if (i < len) s += src(base + i);
-        }
+        for (int j = 0; j < kScanGroups; ++j) s += q[j][0] + q[j][1] + q[j][2] + q[j][3];
     }
     int total;
     wg_scan_incl<kScanThreads>(s, wsum, &total);
-    if (threadIdx.x == 0) tile_sums[(long)blockIdx.y * gridDim.x + blockIdx.x] = total;
+    if (threadIdx.x == 0) sums[(long)blockIdx.y * gridDim.x + blockIdx.x] = total;
 }
 
-// Scan: the tile sums of each row become exclusive prefixes, in place (one
-// 1024-thread work-group per row, the same three stages over chunks of 16384
-// sums: a 2^26-value row in one pass).
-__global__ __launch_bounds__(kScanWide) void scan_tile_sums_kernel(int32_t *tile_sums, int tiles)
+// Scan and down-sweep: each work-group adds up the sums of the chunks before
+// its own (at most kScanChunks, from L2), then scans its chunk's tiles, the
+// last first, each preceded by what the chunk's end is less the tile's own
+// sum.  The up-sweep has just read the chunks in order, so their last tiles
+// are still in the caches; y is stored non-temporally so that it does not
+// evict them.
+__global__ __launch_bounds__(kScanThreads) void scan_downsweep_kernel(const int32_t *x, long n, long chunk,
+                                                                      const int32_t *sums, int32_t *y, int exclusive)
 {
-    constexpr int kChunk = kScanWide * kScanItems;
-    __shared__ int tile[kChunk + kChunk / 16];
-    __shared__ int wsum[kScanWide / 64];
-    const long row = blockIdx.x;
-    int carry = 0;
-    for (int b = 0; b < tiles; b += kChunk)
-        carry = scan_tile<kScanWide>(SrcI32{tile_sums}, row * tiles + b, tiles - b < kChunk ? tiles - b : kChunk,
-                                     tile_sums, carry, true, tile, wsum);
-}
-
-// Down-sweep: each tile scanned again with the prefix of the tiles before it.
-// The tiles are taken last first: the up-sweep has just read them in order,
-// so the last ones are still in the last-level cache; y is stored
-// non-temporally so that it does not evict them (2^26 values: 158 -> 134 us).
-template <class Src>
-__global__ __launch_bounds__(kScanThreads) void scan_downsweep_kernel(Src src, long n, const int32_t *tile_prefix,
-                                                                      int32_t *y, int exclusive)
-{
-    __shared__ int tile[kScanTile + kScanTile / 16];
-    __shared__ int wsum[kScanThreads / 64];
-    const long bx = gridDim.x - 1 - blockIdx.x;
-    const long base = (long)blockIdx.y * n + bx * kScanTile;
-    const long rem = n - bx * kScanTile;
-    scan_tile<kScanThreads, Src, true>(src, base, (int)(rem < kScanTile ? rem : kScanTile), y,
-                                       tile_prefix[(long)blockIdx.y * gridDim.x + bx], exclusive != 0, tile, wsum);
+    __shared__ int wsum[2][kScanThreads / 64];
+    const long c0 = (long)blockIdx.x * chunk;
+    const long len = n - c0 < chunk ? n - c0 : chunk;
+    x += (long)blockIdx.y * n + c0;
+    y += (long)blockIdx.y * n + c0;
+    i32x4 q0[kScanGroups], q1[kScanGroups];
+    long b = (len - 1) / kScanTile * kScanTile;
+    scan_load<kScanThreads>(x + b, len - b, q0);
+    sums += (long)blockIdx.y * gridDim.x;
+    int s = 0, end;
+    for (unsigned i = threadIdx.x; i <= blockIdx.x; i += kScanThreads) s += sums[i];
+    wg_scan_incl<kScanThreads>(s, wsum[0], &end);
+    auto step = [&](i32x4 (&q)[kScanGroups], int *ws) {
+        int before[kScanGroups];
+        end -= scan_before<kScanThreads>(q, before, ws);
+        scan_store<kScanThreads, true>(y + b, len - b, q, before, end, exclusive != 0);
+        b -= kScanTile;
+    };
+    while (true) {
+        if (b == 0) {
+            step(q0, wsum[0]);
+            break;
+        }
+        scan_load<kScanThreads>(x + b - kScanTile, kScanTile, q1);
+        step(q0, wsum[0]);
+        if (b == 0) {
+            step(q1, wsum[1]);
+            break;
+        }
+        scan_load<kScanThreads>(x + b - kScanTile, kScanTile, q0);
+        step(q1, wsum[1]);
+    }
 }
 
 // Rows this long or more, fewer than this many of them, go across work-groups.
 constexpr long kScanLongRow = 4L * kScanTile;
 constexpr int kScanFewRows = 64;
+// Work-groups of a launch over long rows: four per CU, 16 wavefronts, so that
+// all run at once (2^26 values 123.5 us, 11234567 20.9; with 4096 125.2, 22.6).
+constexpr int kScanChunks = 1024;
 
 bool scan_across(int rows, long n) { return rows < kScanFewRows && n > kScanLongRow; }
+
+// Values per chunk: whole tiles, at most about kScanChunks chunks over all rows.
+long scan_chunk(int rows, long n)
+{
+    const long tiles = (n + kScanTile - 1) / kScanTile;
+    return (tiles * rows + kScanChunks - 1) / kScanChunks * kScanTile;
+}
 
 long scan_ws_bytes(int rows, long n)
 {
     if (!scan_across(rows, n)) return 0;
-    return ((long)rows * ((n + kScanTile - 1) / kScanTile) * 4 + 255) / 256 * 256;
+    const long chunk = scan_chunk(rows, n);
+    return ((long)rows * ((n + chunk - 1) / chunk) * 4 + 255) / 256 * 256;
 }
 
-template <class Src>
-hipError_t launch_scan(const Src &src, int rows, long n, int32_t *y, bool exclusive, int32_t *row_totals,
-                       void *ws, hipStream_t st)
+hipError_t launch_scan(const int32_t *x, int rows, long n, int32_t *y, bool exclusive, void *ws, hipStream_t st)
 {
-    if (!scan_across(rows, n) || row_totals) {
+    if (!scan_across(rows, n)) {
         if (rows < 256 && n > kScanTile)
-            launch_kernel(scan_rows_kernel<kScanWide, Src>, dim3((unsigned)rows), dim3(kScanWide), 0, st, src, n, y,
-                          exclusive ? 1 : 0, row_totals);
+            launch_kernel(scan_rows_kernel<kScanWide>, dim3((unsigned)rows), dim3(kScanWide), 0, st, x, n, y,
+                          exclusive ? 1 : 0, (int32_t *)nullptr);
         else
-            launch_kernel(scan_rows_kernel<kScanThreads, Src>, dim3((unsigned)rows), dim3(kScanThreads), 0, st, src,
-                          n, y, exclusive ? 1 : 0, row_totals);
+            launch_kernel(scan_rows_kernel<kScanThreads>, dim3((unsigned)rows), dim3(kScanThreads), 0, st, x, n, y,
+                          exclusive ? 1 : 0, (int32_t *)nullptr);
         return hipGetLastError();
     }
-    const int tiles = (int)((n + kScanTile - 1) / kScanTile);
+    const long chunk = scan_chunk(rows, n);
+    const dim3 grid((unsigned)((n + chunk - 1) / chunk), (unsigned)rows);
     int32_t *sums = static_cast<int32_t *>(ws);
-    launch_kernel(scan_upsweep_kernel<Src>, dim3((unsigned)tiles, (unsigned)rows), dim3(kScanThreads), 0, st, src,
-                  n, sums);
-    launch_kernel(scan_tile_sums_kernel, dim3((unsigned)rows), dim3(kScanWide), 0, st, sums, tiles);
-    launch_kernel(scan_downsweep_kernel<Src>, dim3((unsigned)tiles, (unsigned)rows), dim3(kScanThreads), 0, st,
-                  src, n, static_cast<const int32_t *>(sums), y, exclusive ? 1 : 0);
+    launch_kernel(scan_upsweep_kernel, grid, dim3(kScanThreads), 0, st, x, n, chunk, sums);
+    launch_kernel(scan_downsweep_kernel, grid, dim3(kScanThreads), 0, st, x, n, chunk,
+                  static_cast<const int32_t *>(sums), y, exclusive ? 1 : 0);
     return hipGetLastError();
 }
 
@@ -887,8 +943,8 @@ hipError_t launch_radix(const float *keys, const int32_t *off, int S, long n, in
         a.to_segment = i == 3 && S > 1;
         a.shift = i < 4 ? 8 * i : 0;
         launch_kernel(radix_count_kernel, dim3((unsigned)a.tiles), dim3(kRadixThreads), 0, st, a);
-        launch_kernel(scan_rows_kernel<kScanThreads, SrcI32>, dim3(kRadixBins), dim3(kScanThreads), 0, st,
-                      SrcI32{a.counts}, (long)a.tiles, a.counts, 1, totals);
+        launch_kernel(scan_rows_kernel<kScanThreads>, dim3(kRadixBins), dim3(kScanThreads), 0, st,
+                      a.counts, (long)a.tiles, a.counts, 1, totals);
         launch_kernel(radix_scatter_kernel, dim3((unsigned)a.tiles), dim3(kRadixThreads), 0, st, a);
     }
     return hipGetLastError();
@@ -1425,7 +1481,7 @@ int vision_scan_i32(int rows, long n, const int32_t *x, int32_t *y, int exclusiv
     const long need = vision_scan_workspace_bytes(rows, n);
     if (need < 0) return (int)need;
     if (!ws_ok(ws, ws_bytes, need)) return MICONV_ERR_WORKSPACE;
-    const hipError_t e = launch_scan(SrcI32{x}, rows, n, y, exclusive != 0, (int32_t *)nullptr, ws,
+    const hipError_t e = launch_scan(x, rows, n, y, exclusive != 0, ws,
                                      static_cast<hipStream_t>(stream));
     return e == hipSuccess ? MICONV_OK : set_hip_error(e);
 }
