@@ -45,6 +45,14 @@ PEAK_BF16_MFMA_TFLOPS = 2516.6
 PEAK_HBM_GBS = 8000.0
 
 
+def mfma_peak(kernel, bf16):
+    """The MFMA ceiling of a kernel in TFLOP/s of the convolution's own
+    arithmetic: fp32 layers on split bf16 parts run six bf16 products for each."""
+    if "split3" in kernel:
+        return round(PEAK_BF16_MFMA_TFLOPS / 6, 1)
+    return PEAK_BF16_MFMA_TFLOPS if bf16 else PEAK_FP32_MFMA_TFLOPS
+
+
 def measured_traffic(kernel: str, workload: str):
     """HBM bytes per launch of `kernel` (read + written, calibrated against a
     plain copy) in `workload`, from the committed counter summary
@@ -522,8 +530,8 @@ def stack_record(args, config: int, batch, steps: int, warmup: int, cpu_seconds:
     avg_launch_us = dom["ms"] / dom["launches"] * 1e3
     # The bound is the lower ceiling for the kernel's arithmetic intensity:
     # HBM when its FLOP per algorithmic byte is below the ridge point
-    # (MFMA peak / HBM peak), else the MFMA peak of its dtype.
-    peak = PEAK_BF16_MFMA_TFLOPS if bf16 else PEAK_FP32_MFMA_TFLOPS
+    # (MFMA peak / HBM peak), else the MFMA peak of its arithmetic.
+    peak = mfma_peak(dom_name, bf16)
     ridge = peak * 1e12 / (PEAK_HBM_GBS * 1e9)
     if dom_name.startswith("dw") or dom["flops"] < ridge * dom["bytes"]:
         achieved = dom["bytes"] / (dom["ms"] * 1e-3) / 1e9
@@ -545,7 +553,8 @@ def stack_record(args, config: int, batch, steps: int, warmup: int, cpu_seconds:
     # Stack-wide fraction of roofline: sum over layers of the time the layer
     # needs at the binding peak (MFMA or HBM, whichever is slower for it), over
     # the graph-timed step (and, for reference, over the summed kernel stamps).
-    t_roof = sum(max(d["flops"] / (peak * 1e12), d["bytes"] / (PEAK_HBM_GBS * 1e9)) for d in layers)
+    t_roof = sum(max(d["flops"] / (mfma_peak(d["kernel"], bf16) * 1e12), d["bytes"] / (PEAK_HBM_GBS * 1e9))
+                 for d in layers)
     stack_roof_frac = t_roof / (ms_per_step * 1e-3)
     stack_roof_frac_kernels = t_roof / (float(layer_ms.sum()) * 1e-3)
 
@@ -817,12 +826,7 @@ def vision_record(steps: int, cpu_seconds: float) -> dict:
     fn = lambda s: vision.segmented_argsort(keys, off, True, out=idx, ws=ws, stream=s)  # noqa: E731
     fn(stream)
     ms = _graph_ms(torch, fn, max(steps // 5, 3), stream)
-    passes = 0
-    L = 2048
-    while L < n:
-        passes, L = passes + 1, 2 * L
-    rec["argsort"] = {"n": n, "segments": S, "us": round(ms * 1e3, 1), "Mkeys_per_s": round(n / (ms * 1e3), 1),
-                      "merge_passes": passes}
+    rec["argsort"] = {"n": n, "segments": S, "us": round(ms * 1e3, 1), "Mkeys_per_s": round(n / (ms * 1e3), 1)}
     n = 1 << 26
     # two input/output sets in turn, so that a call does not find the previous
     # call's input in the 256 MB last-level cache
