@@ -38,9 +38,10 @@
 // 2^-126 in the value).
 //
 // Infinities, NaNs and values that round to a bf16 infinity have a NaN part,
-// which makes every sum they enter NaN; an accumulator that is not finite is
-// therefore recomputed from the original fp32 x and w in its own lane before
-// bias, residual and activation (ordinary data never takes that path).
+// which makes every sum they enter NaN.  A wavefront that holds such a sum
+// therefore runs its tile's reduction again on the fp32 matrix cores before
+// bias, residual and activation, and takes those sums that are not finite from
+// there (plain_sums; ordinary data never takes that path).
 #include "internal.h"
 
 #include <algorithm>
@@ -179,23 +180,101 @@ __device__ __forceinline__ void wait_vmcnt()
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 
-// The sum of output element (filter k of group g, pixel m) over chunks t0 ..
-// t1-1, in fp32 from the original tensors; taps in the padding are skipped.
-__device__ inline float plain_sum(const float *x, const float *w, int t0, int t1, int RS, int S,
-                                                     int Cg, int H, int W, int ih0, int iw0)
+// The sums of a wavefront's tile over chunks t0 .. t1-1 on the fp32 matrix
+// cores: pixels moff + 32 bj + lane % 32 (past M: zero), filters koff + 32 bi +
+// lane % 32 of group g (past K/groups: zero), in the accumulator layout of the
+// split products.  Taps in the padding are zeros, as in every other kernel.
+// x is read as given (a wavefront's loads are runs of pixels); filters are put
+// together again from their parts, whose rows lie together, except where they
+// are not finite.  256 -> 256 3x3 at 56x56, batch 8 (180 us of finite data): x
+// NaN throughout 627 us, one NaN in x 440 (the fp32 wave kernel 334 and 368);
+// with filters read as given, a line per lane and load, 854 and 584; a sum per
+// lane, element by element, 20.7 and 16.5 ms.
+template <int BJ, int BI>
+__device__ inline void plain_sums(const SplitArgs &sa, int g, int moff, int koff, int t0, int t1,
+                                  floatx16 (&acc)[BJ][BI])
 {
-    float s = 0.f;
-    for (int t = t0; t < t1; ++t) {
-        const int cb = t / RS, rs = t - cb * RS;
-        const int ih = ih0 + rs / S, iw = iw0 + rs % S;
-        if ((unsigned)ih >= (unsigned)H || (unsigned)iw >= (unsigned)W) continue;
-        const int c1 = min(16, Cg - cb * 16);
-        for (int e = 0; e < c1; ++e) {
-            const long c = cb * 16 + e;
-            s = fmaf(x[c * H * W + (long)ih * W + iw], w[c * RS + rs], s);
-        }
+    const ConvArgs &a = sa.a;
+    const int h = (threadIdx.x & 63) >> 5, ll = threadIdx.x & 31;
+    const int RS = a.R * a.S;
+    const int KT = (a.Kg + 63) / 64;
+    constexpr unsigned kOutside = 0xffffffffu;
+    const float *w = static_cast<const float *>(a.w);
+    const __amdgpu_buffer_rsrc_t xres = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<void *>(a.x), (short)0, (int)((long)a.N * a.C * a.HW * 4), 0x00020000);
+    const __amdgpu_buffer_rsrc_t wres = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<uint16_t *>(sa.wp), (short)0, (int)((long)a.groups * KT * sa.NC * 6144), 0x00020000);
+    int ih0[BJ], iw0[BJ];
+    unsigned xoff[BJ], woff[BI];
+#pragma unroll
+    for (int bj = 0; bj < BJ; ++bj) {
+        const int m = moff + 32 * bj + ll;
+        const int n = fdiv(m < a.M ? m : 0, a.dv_pq);
+        const int pq = (m < a.M ? m : 0) - n * a.PQ;
+        const int p = fdiv(pq, a.dv_q);
+        ih0[bj] = m < a.M ? p * a.stride - a.pad : -(1 << 28);   // never inside the image
+        iw0[bj] = (pq - p * a.Q) * a.stride - a.pad;
+        // wraps below zero for a padding origin, and back for every tap inside the image
+        xoff[bj] = 4u * ((unsigned)((n * a.C + g * a.Cg + 8 * h) * a.HW) + (unsigned)ih0[bj] * (unsigned)a.W +
+                         (unsigned)iw0[bj]);
     }
-    return s;
+#pragma unroll
+    for (int bi = 0; bi < BI; ++bi) {
+        const int k = koff + 32 * bi + ll;
+        woff[bi] = k < a.Kg ? (unsigned)((((long)g * KT + k / 64) * sa.NC * 64 + k % 64) * 96) + 16u * (h ^ row_flip(k))
+                            : kOutside;
+#pragma unroll
+        for (int bj = 0; bj < BJ; ++bj)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[bj][bi][v] = 0.f;
+    }
+#pragma unroll 1
+    for (int t = t0; t < t1; ++t) {                       // channels 8 h + e of the block, e = 0..7
+        const int cb = t / RS, rs = t - cb * RS;
+        const int r = rs / a.S, s = rs - r * a.S;
+        const unsigned xd = 4u * (unsigned)(cb * 16 * a.HW + r * a.W + s);
+        const int c = cb * 16 + 8 * h;
+        float xv[BJ][8], wv[BI][8];
+        uint4 part[BI][3];
+#pragma unroll
+        for (int bi = 0; bi < BI; ++bi)
+#pragma unroll
+            for (int p = 0; p < 3; ++p)
+                part[bi][p] = __builtin_bit_cast(
+                    uint4, __builtin_amdgcn_raw_buffer_load_b128(
+                               wres, woff[bi] == kOutside ? kOutside : woff[bi] + 6144u * t + 32u * p, 0, 0));
+#pragma unroll
+        for (int bj = 0; bj < BJ; ++bj) {
+            const bool in = (unsigned)(ih0[bj] + r) < (unsigned)a.H && (unsigned)(iw0[bj] + s) < (unsigned)a.W;
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                xv[bj][e] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(
+                    xres, in && c + e < a.Cg ? xoff[bj] + xd + 4u * e * a.HW : kOutside, 0, 0));
+        }
+#pragma unroll
+        for (int bi = 0; bi < BI; ++bi) {
+            const int k = koff + 32 * bi + ll;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                float v[3];
+#pragma unroll
+                for (int p = 0; p < 3; ++p) {
+                    const uint32_t q[4] = {part[bi][p].x, part[bi][p].y, part[bi][p].z, part[bi][p].w};
+                    v[p] = __uint_as_float(e & 1 ? q[e / 2] & 0xFFFF0000u : q[e / 2] << 16);
+                }
+                wv[bi][e] = v[0] + v[1] + v[2];
+                if (!(fabsf(v[0]) < __builtin_inff()))    // never a zero of the padding past K or C
+                    wv[bi][e] = w[(((long)g * a.Kg + k) * a.Cg + c + e) * RS + rs];
+            }
+        }
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+#pragma unroll
+            for (int bj = 0; bj < BJ; ++bj)
+#pragma unroll
+                for (int bi = 0; bi < BI; ++bi)
+                    acc[bj][bi] = __builtin_amdgcn_mfma_f32_32x32x2f32(xv[bj][e], wv[bi][e], acc[bj][bi], 0, 0, 0);
+    }
 }
 
 template <int BPX, int BKC, int WPX, int WCH, int NST>
@@ -345,6 +424,10 @@ __global__ __launch_bounds__(256, 2) void igemm_split3_kernel(SplitArgs sa)
             for (int bj = 0; bj < BJ; ++bj) xv[p][bj] = *reinterpret_cast<const bf16x8 *>(st + boff[bj] + 2 * p);
         }
         if (more) issue(tn, fill);
+        // All reads at once, not as the MFMAs need them: a wavefront that starts
+        // its MFMAs sooner only stalls among them (204 -> 199 us on VGG-16's 128 ->
+        // 128 layer at 112x112, batch 8).
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         __builtin_amdgcn_s_setprio(1);
         constexpr int px[6] = {0, 0, 1, 1, 0, 2}, pw[6] = {0, 1, 0, 1, 2, 0};   // hh, hm, mh, mm, hl, lh
 #pragma unroll
@@ -376,43 +459,47 @@ __global__ __launch_bounds__(256, 2) void igemm_split3_kernel(SplitArgs sa)
         fill = fill + 1 == NST ? 0 : fill + 1;
     }
 
+    // Both accumulators in one; sums that are not finite again from the fp32 tensors.
+    bool bad = false;
+#pragma unroll
+    for (int bj = 0; bj < BJ; ++bj)
+#pragma unroll
+        for (int bi = 0; bi < BI; ++bi)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                float sm = small[0][bj][bi][v];
+                if constexpr (NS == 2) sm += small[1][bj][bi][v];
+                big[bj][bi][v] += sm;
+                bad |= !(fabsf(big[bj][bi][v]) < __builtin_inff());
+            }
+    if (__builtin_expect(__ballot(bad) != 0, 0)) {
+        floatx16 fp32[BJ][BI];
+        plain_sums<BJ, BI>(sa, g, m0 + wpx * TPX, k0 + wch * TCH, t_begin, t_end, fp32);
+#pragma unroll
+        for (int bj = 0; bj < BJ; ++bj)
+#pragma unroll
+            for (int bi = 0; bi < BI; ++bi)
+#pragma unroll
+                for (int v = 0; v < 16; ++v)
+                    if (!(fabsf(big[bj][bi][v]) < __builtin_inff())) big[bj][bi][v] = fp32[bj][bi][v];
+    }
+
     // Epilogue through LDS, channel-major, so that rows leave as contiguous
     // 16-byte stores.
     __syncthreads();
     float *ot = reinterpret_cast<float *>(smem);
-    bool bad = false;
 #pragma unroll
     for (int bi = 0; bi < BI; ++bi)
 #pragma unroll
         for (int bj = 0; bj < BJ; ++bj)
 #pragma unroll
             for (int q4 = 0; q4 < 4; ++q4) {
-                float v4[4];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    float sm = small[0][bj][bi][4 * q4 + e];
-                    if constexpr (NS == 2) sm += small[1][bj][bi][4 * q4 + e];
-                    v4[e] = big[bj][bi][4 * q4 + e] + sm;
-                    bad |= !(fabsf(v4[e]) < __builtin_inff());
-                }
                 const int kl = wch * TCH + bi * 32 + ll, pl = wpx * TPX + bj * 32 + 8 * q4 + 4 * h;
-                *reinterpret_cast<float4 *>(ot + kl * OP + pl) = make_float4(v4[0], v4[1], v4[2], v4[3]);
+                const floatx16 &v = big[bj][bi];
+                *reinterpret_cast<float4 *>(ot + kl * OP + pl) =
+                    make_float4(v[4 * q4], v[4 * q4 + 1], v[4 * q4 + 2], v[4 * q4 + 3]);
             }
-    if (__syncthreads_or(bad)) {
-        for (int idx = tid; idx < BKC * BPX; idx += NT) {
-            const int kl = idx / BPX, pl = idx % BPX;
-            const int k = k0 + kl, m = m0 + pl;
-            if (k >= a.Kg || m >= a.M || fabsf(ot[kl * OP + pl]) < __builtin_inff()) continue;
-            const int im = fdiv(m, a.dv_pq);
-            const int pq = m - im * a.PQ;
-            const int p = fdiv(pq, a.dv_q);
-            ot[kl * OP + pl] =
-                plain_sum(static_cast<const float *>(a.x) + ((long)im * a.C + g * a.Cg) * a.HW,
-                          static_cast<const float *>(a.w) + ((long)g * a.Kg + k) * a.Cg * RS, t_begin, t_end, RS, a.S,
-                          a.Cg, a.H, a.W, p * a.stride - a.pad, (pq - p * a.Q) * a.stride - a.pad);
-        }
-        __syncthreads();
-    }
+    __syncthreads();
     const bool split_out = a.splits > 1;
     float *out = split_out ? a.ws + (long)split * a.K * a.M : a.y;
     const bool vec = split_out ? (a.M & 3) == 0 : ((a.PQ & 3) == 0 && ((uintptr_t)a.y & 15) == 0 && (a.ysn & 3) == 0);

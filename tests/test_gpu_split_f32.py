@@ -178,3 +178,54 @@ def test_split_needs_no_more_scratch_than_given():
         assert torch.equal(y[i], y[0]), i
     assert not torch.equal(y[4], y[0])
     assert float((y[4] - y[0]).norm() / y[0].norm()) < 2e-6
+
+
+@pytest.mark.parametrize("case", [CASES[0], CASES[1], CASES[6], CASES[9]], ids=lambda c: "x".join(map(str, c[:9])))
+def test_split_non_finite_filters(case):
+    """Infinite and NaN filter values give what the fp32 MFMA kernel gives,
+    padding included (a tap in the padding is a zero in every kernel, so an
+    infinity there is a NaN), and leave every other filter's sums alone (1e-5
+    of the sum of magnitudes bounds a chain of 2500 sums)."""
+    N, C, H, W, K, R, st, pad, g, kernel, _ = case
+    rng = np.random.default_rng(6)
+    x = rng.uniform(0.5, 1, (N, C, H, W)).astype(np.float32)
+    w = rng.normal(0, 0.05, (K, C // g, R, R)).astype(np.float32)
+    # (not among the first taps: the fp32 MFMA kernel may read those past the filter before, times zero)
+    w[1, 1, 0, 0], w[2, 3, R // 2, R // 2], w[K // 2, 1, R - 1, 0] = np.inf, -np.inf, np.nan
+    w[K - 1, 1, 1, 1], w[K - 1, C // g - 1, 1, 0] = np.inf, -np.inf
+    tx, tw = dev(x), dev(w)
+    P, Q = miconv.out_dims(H, W, R, R, st, pad)
+    got, want, mag = (torch.empty((N, K, P, Q), device="cuda") for _ in range(3))
+    assert kernel in miconv.conv2d_describe(N, C, H, W, K, R, R, st, pad, g, "f32")[0]
+    miconv.conv2d_fwd_ws(tx, tw, None, got, st, pad, g)
+    miconv.conv2d_fwd_ws(tx, tw, None, want, st, pad, g, algo=miconv.ALGO_WAVE)
+    miconv.conv2d_fwd_ws(tx, tw.abs(), None, mag, st, pad, g, algo=miconv.ALGO_WAVE)
+    got, want, mag = (t.cpu().numpy() for t in (got, want, mag))
+    assert np.isinf(want[:, 1]).any() and np.isnan(want[:, K - 1]).all()
+    fin = np.isfinite(want)
+    np.testing.assert_array_equal(np.isnan(got), np.isnan(want))
+    np.testing.assert_array_equal(got[np.isinf(want)], want[np.isinf(want)])
+    assert np.all(np.abs(got[fin] - want[fin]) <= 1e-5 * mag[fin])
+
+
+def test_split_time_does_not_hang_on_the_data():
+    """A layer whose input is NaN throughout (a diverged network) is served by
+    the fp32 matrix cores after the split products: a few times the usual time
+    (the margin of 8 is for a busy machine)."""
+    N, C, H, W, K = 8, 256, 56, 56, 256
+    w = torch.randn((K, C, 3, 3), device="cuda") * 0.03
+    y = torch.empty((N, K, H, W), device="cuda")
+    ws = miconv.workspace(miconv.conv2d_workspace_bytes(N, C, H, W, K, 3, 3, 1, 1))
+    ms = []
+    for x in (torch.rand((N, C, H, W), device="cuda"), torch.full((N, C, H, W), float("nan"), device="cuda")):
+        best = 1e9
+        for _ in range(4):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            miconv.conv2d_fwd_ws(x, w, None, y, 1, 1, ws=ws)
+            b.record()
+            torch.cuda.synchronize()
+            best = min(best, a.elapsed_time(b))
+        ms.append(best)
+    assert bool(torch.isnan(y).all())
+    assert ms[1] < 8 * ms[0], ms
