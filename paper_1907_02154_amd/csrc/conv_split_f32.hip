@@ -33,12 +33,14 @@
 // over all), no LDS bank conflicts.  Three stages of 16-channel chunks leave
 // two work-groups per CU; five stages (one fewer) were slower on every shape.
 //
-// The parts are exact for values down to about 2^-100; of smaller ones the
-// lowest part leaves bf16's range of normal numbers (an error of at most
-// 2^-126 in the value).
+// Both operands are split at 2^24 times their value and the sums scaled back,
+// so that no part of any fp32 value, subnormal ones included, falls below
+// bf16's normal numbers (2^-149 becomes 2^-125), nor any product of parts that
+// counts below fp32's.  The other end pays: values from 2^104 and sums from
+// 2^80 overflow, and are served as infinities are.
 //
-// Infinities, NaNs and values that round to a bf16 infinity have a NaN part,
-// which makes every sum they enter NaN.  A wavefront that holds such a sum
+// Infinities, NaNs and values that overflow have a part that is not finite,
+// which makes every sum they enter NaN or infinite.  A wavefront that holds such a sum
 // therefore runs its tile's reduction again on the fp32 matrix cores before
 // bias, residual and activation, and takes those sums that are not finite from
 // there (plain_sums; ordinary data never takes that path).
@@ -54,7 +56,9 @@ typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __attribute__((address_space(3))) void lds_void_t;
 
-// The three parts of 8 values, packed in pairs.
+constexpr float kScaleUp = 0x1p24f, kScaleDown = 0x1p-24f;
+
+// The three parts of 8 values times kScaleUp, packed in pairs.
 struct Parts {
     uint4 hi, mid, lo;
 };
@@ -64,7 +68,7 @@ __device__ __forceinline__ Parts split8(const float (&v)[8])
     uint32_t d[3][4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-        float a = v[2 * e], b = v[2 * e + 1];
+        float a = v[2 * e] * kScaleUp, b = v[2 * e + 1] * kScaleUp;
 #pragma unroll
         for (int p = 0; p < 3; ++p) {
             const uint32_t q = pack_bf16x2(a, b);
@@ -184,15 +188,17 @@ __device__ __forceinline__ void wait_vmcnt()
 // cores: pixels moff + 32 bj + lane % 32 (past M: zero), filters koff + 32 bi +
 // lane % 32 of group g (past K/groups: zero), in the accumulator layout of the
 // split products.  Taps in the padding are zeros, as in every other kernel.
+// Every four chunks are summed apart, so that the roundings are no more than
+// where the fp32 wave kernel's wavefronts divide the reduction among themselves.
 // x is read as given (a wavefront's loads are runs of pixels); filters are put
 // together again from their parts, whose rows lie together, except where they
 // are not finite.  256 -> 256 3x3 at 56x56, batch 8 (180 us of finite data): x
-// NaN throughout 627 us, one NaN in x 440 (the fp32 wave kernel 334 and 368);
+// NaN throughout 658 us, one NaN in x 477 (the fp32 wave kernel 334 and 368);
 // with filters read as given, a line per lane and load, 854 and 584; a sum per
 // lane, element by element, 20.7 and 16.5 ms.
 template <int BJ, int BI>
 __device__ inline void plain_sums(const SplitArgs &sa, int g, int moff, int koff, int t0, int t1,
-                                  floatx16 (&acc)[BJ][BI])
+                                  floatx16 (&sum)[BJ][BI])
 {
     const ConvArgs &a = sa.a;
     const int h = (threadIdx.x & 63) >> 5, ll = threadIdx.x & 31;
@@ -206,6 +212,7 @@ __device__ inline void plain_sums(const SplitArgs &sa, int g, int moff, int koff
         const_cast<uint16_t *>(sa.wp), (short)0, (int)((long)a.groups * KT * sa.NC * 6144), 0x00020000);
     int ih0[BJ], iw0[BJ];
     unsigned xoff[BJ], woff[BI];
+    floatx16 acc[BJ][BI];
 #pragma unroll
     for (int bj = 0; bj < BJ; ++bj) {
         const int m = moff + 32 * bj + ll;
@@ -226,28 +233,28 @@ __device__ inline void plain_sums(const SplitArgs &sa, int g, int moff, int koff
 #pragma unroll
         for (int bj = 0; bj < BJ; ++bj)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) acc[bj][bi][v] = 0.f;
+            for (int v = 0; v < 16; ++v) acc[bj][bi][v] = sum[bj][bi][v] = 0.f;
     }
 #pragma unroll 1
-    for (int t = t0; t < t1; ++t) {                       // channels 8 h + e of the block, e = 0..7
-        const int cb = t / RS, rs = t - cb * RS;
+    for (int u = 2 * t0; u < 2 * t1; ++u) {               // channels 8 h + 4 (u % 2) + e of chunk u / 2's block
+        const int t = u >> 1, cb = t / RS, rs = t - cb * RS;
         const int r = rs / a.S, s = rs - r * a.S;
-        const unsigned xd = 4u * (unsigned)(cb * 16 * a.HW + r * a.W + s);
-        const int c = cb * 16 + 8 * h;
-        float xv[BJ][8], wv[BI][8];
-        uint4 part[BI][3];
+        const int c = cb * 16 + 8 * h + 4 * (u & 1);
+        const unsigned xd = 4u * (unsigned)((cb * 16 + 4 * (u & 1)) * a.HW + r * a.W + s);
+        float xv[BJ][4], wv[BI][4];
+        uint2 part[BI][3];
 #pragma unroll
         for (int bi = 0; bi < BI; ++bi)
 #pragma unroll
             for (int p = 0; p < 3; ++p)
                 part[bi][p] = __builtin_bit_cast(
-                    uint4, __builtin_amdgcn_raw_buffer_load_b128(
-                               wres, woff[bi] == kOutside ? kOutside : woff[bi] + 6144u * t + 32u * p, 0, 0));
+                    uint2, __builtin_amdgcn_raw_buffer_load_b64(
+                               wres, woff[bi] == kOutside ? kOutside : woff[bi] + 6144u * t + 8u * (u & 1) + 32u * p, 0, 0));
 #pragma unroll
         for (int bj = 0; bj < BJ; ++bj) {
             const bool in = (unsigned)(ih0[bj] + r) < (unsigned)a.H && (unsigned)(iw0[bj] + s) < (unsigned)a.W;
 #pragma unroll
-            for (int e = 0; e < 8; ++e)
+            for (int e = 0; e < 4; ++e)
                 xv[bj][e] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(
                     xres, in && c + e < a.Cg ? xoff[bj] + xd + 4u * e * a.HW : kOutside, 0, 0));
         }
@@ -255,25 +262,35 @@ __device__ inline void plain_sums(const SplitArgs &sa, int g, int moff, int koff
         for (int bi = 0; bi < BI; ++bi) {
             const int k = koff + 32 * bi + ll;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
+            for (int e = 0; e < 4; ++e) {
                 float v[3];
 #pragma unroll
                 for (int p = 0; p < 3; ++p) {
-                    const uint32_t q[4] = {part[bi][p].x, part[bi][p].y, part[bi][p].z, part[bi][p].w};
-                    v[p] = __uint_as_float(e & 1 ? q[e / 2] & 0xFFFF0000u : q[e / 2] << 16);
+                    const uint32_t q = e < 2 ? part[bi][p].x : part[bi][p].y;
+                    v[p] = __uint_as_float(e & 1 ? q & 0xFFFF0000u : q << 16);
                 }
-                wv[bi][e] = v[0] + v[1] + v[2];
+                wv[bi][e] = (v[0] + v[1] + v[2]) * kScaleDown;
                 if (!(fabsf(v[0]) < __builtin_inff()))    // never a zero of the padding past K or C
                     wv[bi][e] = w[(((long)g * a.Kg + k) * a.Cg + c + e) * RS + rs];
             }
         }
 #pragma unroll
-        for (int e = 0; e < 8; ++e)
+        for (int e = 0; e < 4; ++e)
 #pragma unroll
             for (int bj = 0; bj < BJ; ++bj)
 #pragma unroll
                 for (int bi = 0; bi < BI; ++bi)
                     acc[bj][bi] = __builtin_amdgcn_mfma_f32_32x32x2f32(xv[bj][e], wv[bi][e], acc[bj][bi], 0, 0, 0);
+        if (((u - 2 * t0) & 7) == 7 || u + 1 == 2 * t1)
+#pragma unroll
+            for (int bj = 0; bj < BJ; ++bj)
+#pragma unroll
+                for (int bi = 0; bi < BI; ++bi)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) {
+                        sum[bj][bi][v] += acc[bj][bi][v];
+                        acc[bj][bi][v] = 0.f;
+                    }
     }
 }
 
@@ -459,46 +476,43 @@ __global__ __launch_bounds__(256, 2) void igemm_split3_kernel(SplitArgs sa)
         fill = fill + 1 == NST ? 0 : fill + 1;
     }
 
-    // Both accumulators in one; sums that are not finite again from the fp32 tensors.
-    bool bad = false;
-#pragma unroll
-    for (int bj = 0; bj < BJ; ++bj)
-#pragma unroll
-        for (int bi = 0; bi < BI; ++bi)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                float sm = small[0][bj][bi][v];
-                if constexpr (NS == 2) sm += small[1][bj][bi][v];
-                big[bj][bi][v] += sm;
-                bad |= !(fabsf(big[bj][bi][v]) < __builtin_inff());
-            }
-    if (__builtin_expect(__ballot(bad) != 0, 0)) {
-        floatx16 fp32[BJ][BI];
-        plain_sums<BJ, BI>(sa, g, m0 + wpx * TPX, k0 + wch * TCH, t_begin, t_end, fp32);
-#pragma unroll
-        for (int bj = 0; bj < BJ; ++bj)
-#pragma unroll
-            for (int bi = 0; bi < BI; ++bi)
-#pragma unroll
-                for (int v = 0; v < 16; ++v)
-                    if (!(fabsf(big[bj][bi][v]) < __builtin_inff())) big[bj][bi][v] = fp32[bj][bi][v];
-    }
-
     // Epilogue through LDS, channel-major, so that rows leave as contiguous
-    // 16-byte stores.
+    // 16-byte stores: both accumulators in one, at the values' own scale.
     __syncthreads();
     float *ot = reinterpret_cast<float *>(smem);
+    bool bad = false;
+    const auto at = [&](int bj, int bi, int q4) {           // four pixels of a filter
+        return ot + (wch * TCH + bi * 32 + ll) * OP + wpx * TPX + bj * 32 + 8 * q4 + 4 * h;
+    };
 #pragma unroll
     for (int bi = 0; bi < BI; ++bi)
 #pragma unroll
         for (int bj = 0; bj < BJ; ++bj)
 #pragma unroll
             for (int q4 = 0; q4 < 4; ++q4) {
-                const int kl = wch * TCH + bi * 32 + ll, pl = wpx * TPX + bj * 32 + 8 * q4 + 4 * h;
-                const floatx16 &v = big[bj][bi];
-                *reinterpret_cast<float4 *>(ot + kl * OP + pl) =
-                    make_float4(v[4 * q4], v[4 * q4 + 1], v[4 * q4 + 2], v[4 * q4 + 3]);
+                float v4[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    float sm = small[0][bj][bi][4 * q4 + e];
+                    if constexpr (NS == 2) sm += small[1][bj][bi][4 * q4 + e];
+                    v4[e] = (big[bj][bi][4 * q4 + e] + sm) * (kScaleDown * kScaleDown);
+                    bad |= !(fabsf(v4[e]) < __builtin_inff());
+                }
+                *reinterpret_cast<float4 *>(at(bj, bi, q4)) = make_float4(v4[0], v4[1], v4[2], v4[3]);
             }
+    if (__builtin_expect(__ballot(bad) != 0, 0)) {          // each lane's own sums, where they are not finite
+        floatx16 sum[BJ][BI];
+        plain_sums<BJ, BI>(sa, g, m0 + wpx * TPX, k0 + wch * TCH, t_begin, t_end, sum);
+#pragma unroll
+        for (int bj = 0; bj < BJ; ++bj)
+#pragma unroll
+            for (int bi = 0; bi < BI; ++bi)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    float *o = at(bj, bi, v / 4) + v % 4;
+                    if (!(fabsf(*o) < __builtin_inff())) *o = sum[bj][bi][v];
+                }
+    }
     __syncthreads();
     const bool split_out = a.splits > 1;
     float *out = split_out ? a.ws + (long)split * a.K * a.M : a.y;

@@ -229,3 +229,28 @@ def test_split_time_does_not_hang_on_the_data():
         ms.append(best)
     assert bool(torch.isnan(y).all())
     assert ms[1] < 8 * ms[0], ms
+
+
+@pytest.mark.parametrize("ex,ew", [(-115, 100), (-126, 90), (-138, 95), (100, -118), (90, -140), (-60, -60), (60, 40)],
+                         ids=lambda e: "2^%d" % e)
+@pytest.mark.parametrize("case", [ERR_CASES[0], ERR_CASES[2], ERR_CASES[4]], ids=lambda c: "x".join(map(str, c)))
+def test_split_keeps_every_magnitude(case, ex, ew):
+    """x and w far down in fp32's range, subnormal ones included, beside large
+    partners: the error against float64 stays within 1.1 times the fp32 MFMA
+    kernel's, and is at most the 1e-6 that both show on ordinary data (values
+    below 2^-126 are rounded when they are made, which both read alike).
+    (-60, -60) has tiny sums, (60, 40) sums beyond 2^80, which are recomputed."""
+    N, C, H, W, K, R, st = case
+    assert "igemm_split3" in miconv.conv2d_describe(N, C, H, W, K, R, R, st, R // 2, 1, "f32")[0]
+    g = torch.Generator(device="cuda")
+    g.manual_seed(77 + sum(case))
+    x = torch.randn((N, C, H, W), generator=g, device="cuda", dtype=torch.float64).mul_(2.0 ** ex).float()
+    w = torch.randn((K, C, R, R), generator=g, device="cuda", dtype=torch.float64).mul_(2.0 ** ew).float()
+    P, Q = miconv.out_dims(H, W, R, R, st, R // 2)
+    want = _conv64(x, w, st, R // 2)
+    err = {}
+    for algo in (miconv.ALGO_AUTO, miconv.ALGO_WAVE):
+        y = torch.empty((N, K, P, Q), device="cuda")
+        miconv.conv2d_fwd_ws(x, w, None, y, st, R // 2, algo=algo)
+        err[algo] = float((y.double() - want).norm() / want.norm())
+    assert err[miconv.ALGO_AUTO] <= min(1.1 * err[miconv.ALGO_WAVE], 1e-6), err
