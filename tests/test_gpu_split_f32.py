@@ -254,3 +254,44 @@ def test_split_keeps_every_magnitude(case, ex, ew):
         miconv.conv2d_fwd_ws(x, w, None, y, st, R // 2, algo=algo)
         err[algo] = float((y.double() - want).norm() / want.norm())
     assert err[miconv.ALGO_AUTO] <= min(1.1 * err[miconv.ALGO_WAVE], 1e-6), err
+
+
+# kind -> (bits of x, share of x that is not zero, bits of w, share of w): which of the six
+# products carry the result besides hi * hi
+PART_KINDS = {
+    "x_mid": (11, 1.0, 1, 1.0),       # mid * hi
+    "w_mid": (1, 1.0, 11, 1.0),       # hi * mid
+    "mid_mid": (10, 0.05, 10, 0.05),  # and mid * mid
+    "x_lo": (18, 1.0, 1, 0.006),      # lo * hi
+    "w_lo": (1, 0.006, 18, 1.0),      # hi * lo
+}
+
+
+def _part_ints(shape, bits, share, rng):
+    """Odd integers of up to `bits` bits, a share of them kept: the lowest bit
+    is in the lowest part that the size needs (bf16 holds 8 bits, two parts 16)."""
+    v = rng.integers(0, 1 << (bits - 1), shape, dtype=np.int64) * 2 + 1
+    v *= rng.choice((-1, 1), shape)
+    return np.where(rng.random(shape) < share, v, 0).astype(np.float32)
+
+
+@pytest.mark.parametrize("kind", PART_KINDS)
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "x".join(map(str, c[:9])))
+def test_split_parts_bitwise(oracle_lib, case, kind):
+    """Integers that one bf16 cannot hold, with sums of magnitudes below 2^23
+    (every order of summation is exact): a part that is swapped, misplaced or
+    stale shows in every tile, tail, group, copy and split reduction."""
+    N, C, H, W, K, R, st, pad, g, kernel, _ = case
+    assert kernel in miconv.conv2d_describe(N, C, H, W, K, R, R, st, pad, g, "f32")[0]
+    xb, xs, wb, ws = PART_KINDS[kind]
+    rng = np.random.default_rng(1000 + sum(case[:9]))
+    x = _part_ints((N, C, H, W), xb, xs, rng)
+    w = _part_ints((K, C // g, R, R), wb, ws, rng)
+    ref = oracle_lib.conv2d(x, w, None, st, pad, g, False)
+    assert oracle_lib.conv2d(np.abs(x), np.abs(w), None, st, pad, g, False).max() < 2 ** 23
+    tx, tw = dev(x), dev(w)
+    xo = torch.empty(tx.numel() + 1, device="cuda")[1:].view(N, C, H, W).copy_(tx)   # 4-byte reads in the copy
+    for xx in (tx, xo):
+        y = torch.full(ref.shape, float("nan"), device="cuda")
+        miconv.conv2d_fwd_ws(xx, tw, None, y, st, pad, g)
+        np.testing.assert_array_equal(y.cpu().numpy(), ref)
