@@ -1,14 +1,16 @@
 // Dense conv2d in fp32 on the bf16 matrix cores, for layers large enough to
 // be bound by the fp32 MFMA rate.
 //
-// Every fp32 value is the exact sum of three bf16 values: hi = bf16(v),
-// mid = bf16(v - hi), lo = v - hi - mid, each rounded to nearest even, so
-// |mid| <= 2^-9 |hi| and |lo| <= 2^-18 |hi| and nothing is left over (24
-// significand bits in three times 8).  A product is then
+// Every fp32 value is the exact sum of three bf16 values (the bf16x3 scheme of
+// Henry, Tang and Heinecke, 2019): hi = bf16(v), mid = bf16(v - hi), lo = v -
+// hi - mid, each rounded to nearest even, so |mid| <= 2^-8 |v| and |lo| <= 2^-17
+// |v| and nothing is left over (24 significand bits in three times 8).  A
+// product is then
 //   x w = xh wh + (xh wm + xm wh + xm wm + xh wl + xl wh) + (xm wl + xl wm + xl wl)
-// and the last bracket is below 2^-26 of |x w|, a quarter of fp32's own
-// rounding of the product: it is dropped.  Six bf16 MFMAs of 16 taps replace
-// eight fp32 MFMAs of 2 taps: 192 cycles per 32 x 32 x 16 block instead of 512.
+// and the last bracket, at most 2^-24 of |x w| (about 2^-28 on random data), is
+// dropped: no more than fp32's own rounding of the product.  Six bf16 MFMAs of
+// 16 taps replace eight fp32 MFMAs of 2 taps: 192 cycles per 32 x 32 x 16 block
+// instead of 512.
 // xh wh goes to one fp32 accumulator and the five small products to another,
 // so the roundings of the small ones do not add to the large sum's: against
 // 64 bits the result is no further off than the fp32 MFMA kernel's (measured

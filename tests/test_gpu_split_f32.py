@@ -295,3 +295,21 @@ def test_split_parts_bitwise(oracle_lib, case, kind):
         y = torch.full(ref.shape, float("nan"), device="cuda")
         miconv.conv2d_fwd_ws(xx, tw, None, y, st, pad, g)
         np.testing.assert_array_equal(y.cpu().numpy(), ref)
+
+
+@pytest.mark.parametrize("case", ERR_CASES, ids=lambda c: "x".join(map(str, c)))
+def test_split_dropped_products_at_their_largest(case):
+    """x = w = 0x1.00ff8p0 throughout: the three products that are left out are
+    at their largest, 2^-24 of the whole, and all of one sign.  The error
+    against float64 is at most that above the fp32 MFMA kernel's."""
+    N, C, H, W, K, R, st = case
+    v = float.fromhex("0x1.00ff8p0")
+    x, w = torch.full((N, C, H, W), v, device="cuda"), torch.full((K, C, R, R), v, device="cuda")
+    P, Q = miconv.out_dims(H, W, R, R, st, R // 2)
+    want = _conv64(x, w, st, R // 2)
+    err = {}
+    for algo in (miconv.ALGO_AUTO, miconv.ALGO_WAVE):
+        y = torch.empty((N, K, P, Q), device="cuda")
+        miconv.conv2d_fwd_ws(x, w, None, y, st, R // 2, algo=algo)
+        err[algo] = float((y.double() - want).norm() / want.norm())
+    assert err[miconv.ALGO_AUTO] <= 1.1 * err[miconv.ALGO_WAVE] + 2.0 ** -24, err
