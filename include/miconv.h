@@ -61,8 +61,8 @@ enum miconv_status {
     MICONV_ERR_TOO_LARGE = -5,   /* a tensor exceeds 2^31-1 elements */
     MICONV_ERR_ALIGN = -6,       /* a pointer is not aligned to its element size */
     MICONV_ERR_HIP = -7,         /* a HIP call failed; see miconv_last_hip_error() */
-    MICONV_ERR_WORKSPACE = -8    /* workspace missing, smaller than conv2d_workspace_bytes
-                                    reports, or not 256-byte aligned */
+    MICONV_ERR_WORKSPACE = -8    /* workspace missing or smaller than any plan of the call needs
+                                    (conv2d_workspace_bytes always does), or not 256-byte aligned */
 };
 
 /* What a dense call may use besides its tensors, which decides its kernel
@@ -172,7 +172,8 @@ long conv2d_workspace_bytes(int N, int C, int H, int W, int K, int R, int S, int
  * enqueued; they use it until they complete on `stream`, so concurrent calls
  * need distinct workspaces.  A workspace below conv2d_workspace_bytes that
  * still holds a slower plan's scratch (fp32 layers that would run on a split
- * copy of x) runs that plan; too small for any, or unaligned:
+ * copy of x; NULL counts as 0 bytes) runs that plan; too small for any, or
+ * not 256-byte aligned where conv2d_workspace_bytes is not 0:
  * MICONV_ERR_WORKSPACE, nothing enqueued.  Everything else as conv2d_fwd_ex. */
 int conv2d_fwd_ws(int N, int C, int H, int W, int K, int R, int S, int stride, int pad, int groups,
                   int dtype, int algo, const void *x, const void *w, const float *bias, const float *res,
@@ -184,8 +185,8 @@ int conv2d_fwd_ws(int N, int C, int H, int W, int K, int R, int S, int stride, i
  * fixed scratch array of MICONV_NOALLOC_SCRATCH_BYTES inside the library's
  * device code, one per GPU, held from its first use on that GPU until the
  * process ends.  Allocates nothing (no hipMalloc, hipFree or allocating
- * library routine) and synchronises nothing.  A plan that needs more scratch
- * than that (conv2d_workspace_bytes reports it) fails with
+ * library routine) and synchronises nothing.  A call for which every plan
+ * needs more scratch than that (as conv2d_fwd_ws chooses among them) fails with
  * MICONV_ERR_WORKSPACE and enqueues nothing.  Every call on one GPU shares
  * its scratch: calls that can overlap on one GPU (other streams, other
  * threads, or a graph replay of one) race on it and must be serialised by the

@@ -669,7 +669,9 @@ int conv2d_fwd_ws(int N, int C, int H, int W, int K, int R, int S, int stride, i
                   float *y, long y_image_stride, int relu, void *ws, size_t ws_bytes, void *stream)
 {
     Resolved r;
-    const size_t have = ws && (uintptr_t)ws % 256 == 0 ? ws_bytes : 0;
+    // a workspace that is not aligned is an error where the layer's fastest plan
+    // needs one; only its size chooses a slower plan
+    const size_t have = !ws ? 0 : (uintptr_t)ws % 256 ? kNoLimit : ws_bytes;
     const int rc = resolve_ex(MODE_SCRATCH, N, C, H, W, K, R, S, stride, pad, groups, dtype, algo, x, w,
                               bias, res, y, y_image_stride, relu, &r, have);
     return rc != MICONV_OK ? rc : run(r, ws, ws_bytes, static_cast<hipStream_t>(stream));

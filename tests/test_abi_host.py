@@ -177,6 +177,19 @@ def test_ws_entry_point_checks_the_workspace_first(L):
         miconv.ERR_UNSUPPORTED
 
 
+def test_ws_alignment_is_checked_where_a_slower_plan_needs_no_workspace(L):
+    """An fp32 layer whose fastest plan takes scratch and whose next takes
+    none: a workspace that is not 256-byte aligned is refused whatever its
+    size, not taken for a missing one."""
+    shape = (16, 128, 56, 56, 256, 3, 3, 1, 1, 1)
+    need = L.conv2d_workspace_bytes(*shape, 0, 0)
+    assert need > 0 and L.conv2d_workspace_bytes(*shape, 0, miconv.ALGO_WAVE) == 0
+    A = miconv.ALGO_AUTO
+    for n in (need, need - 1, 2 * need, 0):
+        assert L.conv2d_fwd_ws(*shape, 0, A, FAKE, FAKE, None, None, FAKE, 0, 0, FAKE + 16, n, None) == \
+            miconv.ERR_WORKSPACE, n
+
+
 SCRATCH_KERNELS = ("splitk_reduce", "nchw_to_nhwc", "pack_")
 
 
