@@ -392,6 +392,15 @@ __device__ __forceinline__ uint64_t match_digit(uint32_t d)
     return ((uint64_t)hi << 32) | lo;
 }
 
+// The wavefront's lanes meet: what each has read from or written to LDS before
+// comes before what any of them does after.  The hardware runs them in step;
+// this holds the compiler to it (no instruction).
+__device__ __forceinline__ void wave_step()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 __device__ __forceinline__ int lanes_before(uint64_t set)
 {
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(set >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)set, 0));
@@ -418,7 +427,9 @@ __device__ __forceinline__ void lds_radix_pass(uint32_t (&x)[ITEMS], int (&v)[IT
         const int before = lanes_before(same);
         const int c = cnt[wid][d];
         rank[r] = c + before;
+        wave_step();                           // every lane has read the counters
         if (before == 0) cnt[wid][d] = (uint16_t)(c + __popcll(same));
+        wave_step();                           // and the next round reads them written
     }
     __syncthreads();
     int mine = 0, total;
@@ -850,7 +861,9 @@ __global__ __launch_bounds__(kRadixThreads, 4) void radix_scatter_kernel(RadixAr
         const int before = lanes_before(same);
         const int c = cnt[wid][d];
         rank[r] = c + before;
+        wave_step();                           // as in lds_radix_pass
         if (ok && before == 0) cnt[wid][d] = c + __popcll(same);
+        wave_step();
     }
     __syncthreads();
     // first local slot of every digit, and of every wavefront's share of it
