@@ -88,7 +88,8 @@ int vision_segmented_argsort(long n, int segments, const float *keys, const int3
  * out is -1 (the output is first set invalid as a whole, Sec. 4.3).
  * Pipeline: one pass over the rows sets out to -1 and collects the
  * candidates, chunk by chunk; one work-group per image picks the topk best
- * (radix select) and ranks them; a kernel grid over (candidate block,
+ * (radix select; of more than 65536 rows from the best of every slice, which
+ * other work-groups have picked) and ranks them; a kernel grid over (candidate block,
  * candidate block, image) computes which later candidate
  * each candidate suppresses as 64-bit masks (the innermost loop on threads,
  * the loop above it on work-groups, images on the grid); one wavefront per

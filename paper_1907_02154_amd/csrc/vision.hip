@@ -16,6 +16,8 @@
 #include "../../include/miconv.h"
 #include "../../include/mivision.h"
 
+#include <algorithm>
+#include <cmath>
 
 namespace miconv {
 namespace {
@@ -1040,6 +1042,8 @@ struct NmsArgs {
     float overlap, valid;
     int id_index, score_index, coord_start, force;
     int chunks;        // per image
+    int slice, slices; // chunks per slice and slices per image of the first of two picks
+                       // (one pick: 1, chunks)
     uint32_t *ckey;           // [B][N]: each chunk's candidates from its first row's slot on: key bits
     int32_t *corig;           // and input rows, in row order
     int32_t *ccount;          // [B][chunks] candidates of each chunk
@@ -1121,36 +1125,70 @@ __device__ __forceinline__ float4 load_box(const NmsArgs &a, int b, int i, float
 // of 24564 rows (2400 candidates), where a segmented argsort of all of them
 // and a gathering launch took 31 (box_nms of one image 54 -> 35 us, of 26
 // images of 20565 rows 82 -> 32).
+//   With many rows (kNmsOnePick) a first launch (SLICE), one work-group per
+// slice of an image's chunks, leaves the best cand_max of every slice in the
+// slice's first slots, in row order; the pick then reads one list per slice.
 constexpr int kPickThreads = 1024;
 constexpr int kPickWaves = kPickThreads / 64;
 constexpr int kPickItems = kNmsMax / kPickThreads;     // per thread in the radix passes
 constexpr int kPickCount = 512;                        // most that are ranked by comparing
 
+// Images of more rows are picked in two launches, through slices of sqrt(rows *
+// cand_max) rows, where both launches' work-groups read about as many
+// candidates (all rows valid, best 400 of one image, before -> with it: 100
+// thousand rows 197 -> 103 us, 200 thousand 343 -> 120, a million 1367 -> 173;
+// best 4096 of 200 thousand 867 -> 694; best 400 of 32 images of 100 thousand
+// 247 -> 152; a tenth of 200 thousand valid 109 -> 95).  At 30000 rows the one
+// launch takes 111.
+constexpr int kNmsOnePick = 1 << 16;
+
+int nms_slice_chunks(int N, int cand_max)
+{
+    if (N <= kNmsOnePick || cand_max < 1) return 1;
+    return std::max(1, (int)(std::sqrt((double)N * cand_max) / kNmsChunk + 0.5));
+}
+
+template <bool SLICE>
 __global__ __launch_bounds__(kPickThreads) void nms_pick_kernel(NmsArgs a)
 {
     __shared__ uint32_t key[kNmsMax];                  // picked: key bits, input rows
     __shared__ int32_t row[kNmsMax];
-    __shared__ uint16_t sv[kNmsMax];
-    __shared__ uint16_t cnt[kPickWaves][256];
+    __shared__ uint16_t sv[SLICE ? 1 : kNmsMax];       // ranking
+    __shared__ uint16_t cnt[SLICE ? 1 : kPickWaves][256];
     __shared__ uint32_t hist[2048];
     __shared__ int wsum[kPickWaves];
     __shared__ int wlt[kPickWaves], weq[kPickWaves];
     __shared__ uint32_t s_digit;
     __shared__ int s_left, s_in;
     const int t = threadIdx.x, lane = t & 63, wid = t >> 6;
-    const int b = blockIdx.x;
-    const uint32_t *ck = a.ckey + (long)b * a.N;
-    const int32_t *cr = a.corig + (long)b * a.N;
-    const int32_t *cc = a.ccount + (long)b * a.chunks;
-    // wavefront w looks after a contiguous range of chunks
-    const int per = (a.chunks + kPickWaves - 1) / kPickWaves;
-    const int c0 = min(a.chunks, wid * per), c1 = min(a.chunks, c0 + per);
-    auto chunk_count = [&](int c) {                    // never past the chunk's rows
-        const int n = min(kNmsChunk, a.N - c * kNmsChunk);
-        return min(max(cc[c], 0), n);
+    // the lists this work-group picks from: the chunks of a slice, or the slices of an image
+    const int b = SLICE ? blockIdx.x / a.slices : blockIdx.x;
+    const int sl = SLICE ? blockIdx.x - b * a.slices : 0;
+    const int step = SLICE ? 1 : a.slice;              // chunks per list
+    const int lists = SLICE ? min(a.slice, a.chunks - sl * a.slice) : a.slices;
+    const int pitch = step * kNmsChunk;                // rows per list
+    const int row0 = sl * a.slice * kNmsChunk;
+    uint32_t *ck = a.ckey + (long)b * a.N + row0;
+    int32_t *cr = a.corig + (long)b * a.N + row0;
+    int32_t *cc = a.ccount + (long)b * a.chunks + sl * a.slice;
+    // Wavefront w looks after a contiguous range of pieces, lists or (of fewer
+    // than 16) equal parts of them: n candidates from slot `at` on.
+    const int parts = lists < kPickWaves ? kPickWaves / lists : 1;
+    const int per = (lists * parts + kPickWaves - 1) / kPickWaves;
+    const int c0 = min(lists * parts, wid * per), c1 = min(lists * parts, c0 + per);
+    struct Piece {
+        int at, n;
+    };
+    auto piece = [&](int c) {
+        const int l = parts == 1 ? c : c / parts, part = c - l * parts;
+        // never past the list's rows
+        const int n = min(max(cc[l * step], 0), min(pitch, a.N - row0 - l * pitch));
+        if (parts == 1) return Piece{l * pitch, n};
+        const int lo = n * part / parts;
+        return Piece{l * pitch + lo, n * (part + 1) / parts - lo};
     };
     int mine = 0, total;
-    for (int c = c0 + lane; c < c1; c += 64) mine += chunk_count(c);
+    for (int c = c0 + lane; c < c1; c += 64) mine += piece(c).n;
     wg_scan_incl<kPickThreads>(mine, wsum, &total);
     const int want = min(total, a.cand_max);
     // last: the largest key that is taken, and how many of its equals are
@@ -1167,9 +1205,9 @@ __global__ __launch_bounds__(kPickThreads) void nms_pick_kernel(NmsArgs a)
             hist[t + 1024] = 0;
             __syncthreads();
             for (int c = c0; c < c1; ++c) {
-                const int n = chunk_count(c);
-                for (int i = lane; i < n; i += 64) {
-                    const uint32_t k = ck[c * kNmsChunk + i];
+                const Piece pc = piece(c);
+                for (int i = lane; i < pc.n; i += 64) {
+                    const uint32_t k = ck[pc.at + i];
                     if ((k & known) == prefix) atomicAdd(&hist[(k >> shift) & dm], 1u);
                 }
             }
@@ -1205,9 +1243,9 @@ __global__ __launch_bounds__(kPickThreads) void nms_pick_kernel(NmsArgs a)
     // gather in row order: count per wavefront, then place
     int lt = 0, eq = 0;
     for (int c = c0; c < c1; ++c) {
-        const int n = chunk_count(c);
-        for (int i = lane; i < n; i += 64) {
-            const uint32_t k = ck[c * kNmsChunk + i];
+        const Piece pc = piece(c);
+        for (int i = lane; i < pc.n; i += 64) {
+            const uint32_t k = ck[pc.at + i];
             lt += k < last;
             eq += k == last;
         }
@@ -1228,11 +1266,12 @@ __global__ __launch_bounds__(kPickThreads) void nms_pick_kernel(NmsArgs a)
         eq += weq[w];
     }
     for (int c = c0; c < c1; ++c) {
-        const int n = chunk_count(c);
+        const Piece pc = piece(c);
+        const int n = pc.n;
         for (int i0 = 0; i0 < n; i0 += 64) {
             const int i = i0 + lane;
-            const uint32_t k = i < n ? ck[c * kNmsChunk + i] : 0xffffffffu;
-            const int32_t r = i < n ? cr[c * kNmsChunk + i] : 0;
+            const uint32_t k = i < n ? ck[pc.at + i] : 0xffffffffu;
+            const int32_t r = i < n ? cr[pc.at + i] : 0;
             const uint64_t bl = __ballot(i < n && k < last), be = __ballot(i < n && k == last);
             const int nl = lt + lanes_before(bl), ne = eq + lanes_before(be);
             const bool take = i < n && (k < last || (k == last && ne < equals));
@@ -1245,7 +1284,15 @@ __global__ __launch_bounds__(kPickThreads) void nms_pick_kernel(NmsArgs a)
             eq += __popcll(be);
         }
     }
-    __syncthreads();
+    __syncthreads();                                   // and every read of the lists is done
+    if constexpr (SLICE) {
+        for (int i = t; i < want; i += kPickThreads) {
+            ck[i] = key[i];
+            cr[i] = row[i];
+        }
+        if (t == 0) cc[0] = want;
+        return;
+    }
     auto emit = [&](int rank, int i) {
         float c;
         const long o = (long)b * a.mrows + rank;
@@ -1559,6 +1606,8 @@ int vision_box_nms(int batch, int num, int width, const float *data, float *out,
     a.coord_start = coord_start;
     a.force = force_suppress != 0;
     a.chunks = (num + kNmsChunk - 1) / kNmsChunk;
+    a.slice = nms_slice_chunks(num, cap);
+    a.slices = (a.chunks + a.slice - 1) / a.slice;
     a.ckey = reinterpret_cast<uint32_t *>(w + l.ckey);
     a.corig = reinterpret_cast<int32_t *>(w + l.corig);
     a.ccount = reinterpret_cast<int32_t *>(w + l.ccount);
@@ -1569,7 +1618,9 @@ int vision_box_nms(int batch, int num, int width, const float *data, float *out,
     a.mask = reinterpret_cast<uint64_t *>(w + l.mask);
     launch_kernel(nms_collect_kernel, dim3((unsigned)((long)batch * a.chunks)), dim3(256), 0, st, a);
     if (a.capw > 0) {   // topk == 0: no candidate, the output stays invalid
-        launch_kernel(nms_pick_kernel, dim3((unsigned)batch), dim3(kPickThreads), 0, st, a);
+        if (a.slices < a.chunks)
+            launch_kernel(nms_pick_kernel<true>, dim3((unsigned)(batch * a.slices)), dim3(kPickThreads), 0, st, a);
+        launch_kernel(nms_pick_kernel<false>, dim3((unsigned)batch), dim3(kPickThreads), 0, st, a);
         launch_kernel(nms_mask_kernel, dim3((unsigned)a.capw, (unsigned)a.capw, (unsigned)batch), dim3(256), 0, st,
                       a);
         launch_kernel(nms_sweep_kernel, dim3((unsigned)batch), dim3(kSweepThreads), 0, st, a);

@@ -213,6 +213,37 @@ def test_box_nms_pick_bitwise(oracle_lib, case):
         _check_nms(oracle_lib, data, overlap_thresh=0.45, valid_thresh=valid, topk=topk)
 
 
+# B, rows, share of valid rows, distinct scores (0: all differ), topk: images picked through slices
+SLICE_CASES = [
+    (1, 65536, 1.0, 0, 400),          # the most rows picked at once
+    (1, 65537, 1.0, 0, 400),          # one row past it, in a chunk and a slice of its own
+    (1, 65537, 1.0, 3, 4096),         # the largest topk; the cut falls among equal scores
+    (2, 80000, 1.0, 4, 700),
+    (1, 150001, 1.0, 2, 1),
+    (1, 200000, 1.0, 5, 1000),        # ties across slices
+    (3, 100000, 0.001, 0, 400),       # fewer candidates than topk
+    (1, 300000, 0.02, 0, 100),
+]
+
+
+@pytest.mark.parametrize("case", SLICE_CASES)
+def test_box_nms_slices_bitwise(oracle_lib, case):
+    B, N, share, distinct, topk = case
+    rng = np.random.default_rng(N + topk)
+    s = rng.random((B, N), dtype=np.float32) * 0.9 + 0.05
+    if distinct:
+        s = (rng.integers(1, distinct + 1, (B, N)) / np.float32(8)).astype(np.float32)
+    s[rng.random((B, N)) >= share] = 0
+    if B > 1:
+        s[1, : N // 2] = 0            # whole slices without a candidate
+    xy = rng.random((B, N, 2), dtype=np.float32)
+    wh = rng.random((B, N, 2), dtype=np.float32) * np.float32(0.3)
+    data = np.concatenate([rng.integers(0, 2, (B, N, 1)).astype(np.float32), s[..., None], xy, xy + wh], axis=2)
+    ref = oracle_lib.vision.box_nms(data, 0.3, 0.01, topk=topk)
+    got = vision.box_nms(dev(data), 0.3, 0.01, topk)
+    np.testing.assert_array_equal(got.cpu().numpy(), ref)
+
+
 def test_box_nms_iou_rounding_at_threshold(oracle_lib):
     """4096 images of two same-class boxes whose IoU lies within a few ulps
     of the 0.5 threshold (B is A shifted right by about a third of its
