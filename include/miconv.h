@@ -326,8 +326,11 @@ typedef struct miconv_conv_desc {
 typedef struct miconv_stack miconv_stack;
 
 /* Validate and plan n layers (each as its entry point would); allocate the
- * executor, its packed filters and its workspace on the current device.  On error
- * nothing is allocated and *out is NULL. */
+ * executor, its packed filters and its workspace on the current device: the
+ * largest layer's conv2d_fwd_ws scratch less the filters, twice that if layers
+ * can overlap (an fp32 layer on a split copy of x takes 6 bytes per input value,
+ * up to 2 GiB).  Where that cannot be allocated, plans with less scratch are
+ * taken.  On error nothing is allocated and *out is NULL. */
 int miconv_stack_create(const miconv_conv_desc *layers, int n, miconv_stack **out);
 
 /* Number of layers. */

@@ -251,16 +251,10 @@ int capture_on(miconv_stack *s, int steps, int timed, hipStream_t st)
     return MICONV_OK;
 }
 
-}  // namespace
-
-extern "C" {
-
-int miconv_stack_create(const miconv_conv_desc *layers, int n, miconv_stack **out)
+// The executor for n layers whose plans take ws_limit bytes of scratch at most
+// where a plan with less serves the layer as well.
+int create_stack(const miconv_conv_desc *layers, int n, size_t ws_limit, miconv_stack **out)
 {
-    if (!out) return MICONV_ERR_NULL;
-    *out = nullptr;
-    if (n <= 0) return MICONV_ERR_SHAPE;
-    if (!layers) return MICONV_ERR_NULL;
     miconv_stack *s = new (std::nothrow) miconv_stack;
     if (!s) return MICONV_ERR_HIP;
     hipError_t e = hipGetDevice(&s->device);
@@ -274,7 +268,7 @@ int miconv_stack_create(const miconv_conv_desc *layers, int n, miconv_stack **ou
         Resolved r;
         int rc = resolve(d.op, MICONV_ALGO_AUTO, MODE_SCRATCH | MODE_PREPACK, d.N, d.C, d.H, d.W, d.K, d.R,
                          d.S, d.stride, d.pad, d.groups, d.x, d.w, d.bias, static_cast<float *>(d.y), d.relu,
-                         &r, d.layout);
+                         &r, d.layout, ws_limit);
         if (rc == MICONV_OK) rc = set_output_stride(r, d.y_image_stride);
         if (rc == MICONV_OK) rc = set_residual(r, static_cast<const float *>(d.res));
         if (rc != MICONV_OK) {
@@ -331,6 +325,26 @@ int miconv_stack_create(const miconv_conv_desc *layers, int n, miconv_stack **ou
     }
     *out = s;
     return MICONV_OK;
+}
+
+}  // namespace
+
+extern "C" {
+
+int miconv_stack_create(const miconv_conv_desc *layers, int n, miconv_stack **out)
+{
+    if (!out) return MICONV_ERR_NULL;
+    *out = nullptr;
+    if (n <= 0) return MICONV_ERR_SHAPE;
+    if (!layers) return MICONV_ERR_NULL;
+    int rc = create_stack(layers, n, kNoLimit, out);
+    if (rc == MICONV_ERR_HIP && miconv_last_hip_error() == hipErrorOutOfMemory) {
+        // once more without the plans that are only faster (fp32 layers on a
+        // split copy of x, 6 bytes of scratch per input value)
+        hipGetLastError();
+        rc = create_stack(layers, n, 0, out);
+    }
+    return rc;
 }
 
 int miconv_stack_size(const miconv_stack *s)
