@@ -57,7 +57,8 @@ def measured_traffic(kernel: str, workload: str):
     """HBM bytes per launch of `kernel` (read + written, calibrated against a
     plain copy) in `workload`, from the committed counter summary
     profiles/traffic_<workload>.txt, or None when it has no line for this
-    kernel or the kernel's source changed since the counters were taken."""
+    kernel, its source is not known, or the source changed since the counters
+    were taken."""
     from paper_1907_02154_amd.traffic import source_sha
     path = os.path.join(ROOT, "profiles", f"traffic_{workload}.txt")
     if not os.path.exists(path):
@@ -68,7 +69,8 @@ def measured_traffic(kernel: str, workload: str):
                 continue
             parts = line.rstrip("\n").split("\t")
             if parts[0] == kernel and len(parts) >= 4:
-                if parts[1] != source_sha(kernel):
+                sha = source_sha(kernel)
+                if sha == "-" or parts[1] != sha:
                     return None
                 return int(parts[2]) + int(parts[3])
     return None

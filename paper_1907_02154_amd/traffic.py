@@ -68,6 +68,24 @@ SOURCES = {
     "pack_wave_kernel": "pack.hip",
     "stem7_bf16_kernel": "conv_stem_bf16.hip",
     "pack_stem_kernel": "conv_stem_bf16.hip",
+    "nchw_to_nhwc_sampled_bf16_kernel": "conv_nhwc_bf16.hip",
+    "igemm_split3_kernel": "conv_split_f32.hip",
+    "split3_copy_kernel": "conv_split_f32.hip",
+    "split3_pack_kernel": "conv_split_f32.hip",
+    "add_act_kernel": "glue.hip",
+    "add_act_vec4_kernel": "glue.hip",
+    "cast_bf16_kernel": "glue.hip",
+    "nms_collect_kernel": "vision.hip",
+    "nms_mask_kernel": "vision.hip",
+    "nms_pick_kernel": "vision.hip",
+    "nms_sweep_kernel": "vision.hip",
+    "radix_count_kernel": "vision.hip",
+    "radix_scatter_kernel": "vision.hip",
+    "scan_downsweep_kernel": "vision.hip",
+    "scan_rows_kernel": "vision.hip",
+    "scan_upsweep_kernel": "vision.hip",
+    "segsort_merge_kernel": "vision.hip",
+    "segsort_tile_kernel": "vision.hip",
 }
 
 

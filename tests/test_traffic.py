@@ -55,3 +55,34 @@ def test_counter_means_filtered(tmp_path):
     assert lines[0].startswith("igemm_wave_f32_kernel<1, 1, 8, 1, 1>\tsource_sha1 ") and lines[0].endswith(
         "dispatches 2")
     assert "\tGRBM_GUI_ACTIVE\t60.0" in lines and "\tSQ_INSTS_MFMA\t200.0" in lines
+
+
+def test_every_kernel_has_its_source():
+    """Every kernel of the library maps to the file that defines it, so that a
+    counter summary goes out of date with its source."""
+    import glob
+    import re
+
+    from paper_1907_02154_amd import traffic as tr
+    found = {}
+    for path in glob.glob(os.path.join(tr.CSRC, "*.h*")):
+        with open(path) as f:
+            for name in re.findall(r"__global__(?:\s+__launch_bounds__\([^)]*\))?\s+void\s+(\w+)\s*\(", f.read()):
+                found[name] = os.path.basename(path)
+    assert "igemm_split3_kernel" in found and len(found) > 40
+    assert {k: v for k, v in found.items() if tr.SOURCES.get(k) != v} == {}
+    assert set(tr.SOURCES) == set(found)
+
+
+def test_measured_traffic_needs_a_known_source(tmp_path, monkeypatch):
+    """A counter line of a kernel whose source is not known is never current."""
+    sys.path.insert(0, ROOT)
+    import bench
+    from paper_1907_02154_amd.traffic import source_sha
+    os.makedirs(tmp_path / "profiles")
+    known = "splitk_reduce_kernel"
+    (tmp_path / "profiles" / "traffic_w.txt").write_text(
+        f"no_such_kernel<1>\t-\t10\t20\t1\t1\t3\n{known}\t{source_sha(known)}\t10\t20\t1\t1\t3\n")
+    monkeypatch.setattr(bench, "ROOT", str(tmp_path))
+    assert bench.measured_traffic("no_such_kernel<1>", "w") is None
+    assert bench.measured_traffic(known, "w") == 30
