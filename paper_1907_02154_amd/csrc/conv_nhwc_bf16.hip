@@ -211,8 +211,9 @@ __global__ __launch_bounds__(256) void nchw_to_nhwc_plane_bf16_kernel(NhwcCopyAr
 // A call's filter packing and copy in one launch: the first work-groups pack,
 // the others copy (RV as in nchw_to_nhwc_bf16_kernel, 0 the whole-plane copy).
 // Neither fills the chip for long, and the conv waits for both: 256 -> 256 3x3
-// filters and a 6.4 MB x took 10 us as two launches (gathering pack), 5.1 us as
-// one; the 3x3 layer of 14x14 planes at batch 64 32.2 -> 27.5 us a call.
+// filters and a 6.4 MB x take 7.3 us as one (kernel time in a trace; 10.8 as a
+// gathering pack and a copy); the 3x3 layer of 14x14 planes at batch 64 32.2 ->
+// 27.5 us a call.
 template <int RV>
 __global__ __launch_bounds__(256) void pack_nchw_to_nhwc_bf16_kernel(PackRuns p, NhwcCopyArgs a)
 {

@@ -494,7 +494,8 @@ struct TileArgs {
 };
 
 // ITEMS per thread: blocks of 8192 positions (16; 70 KB of LDS, two
-// work-groups per CU), 4096 or 2048.
+// work-groups per CU), 4096 or 2048.  Two work-groups leave a thread 128 VGPRs:
+// with 16 items the compiler spills 20 of them (84 bytes of scratch per lane).
 template <int ITEMS>
 __global__ __launch_bounds__(kTileThreads, 4) void segsort_tile_kernel(TileArgs a)
 {
@@ -613,9 +614,9 @@ __global__ __launch_bounds__(kTileThreads, 4) void segsort_tile_kernel(TileArgs 
 // counted from the segment's first block, pairwise, so a segment over m blocks
 // is finished after ceil(log2 m) passes wherever it lies, and segments that
 // are finished are not touched: a pass moves only what is still unsorted.
-// 2^22 keys in 4096 segments take 26 us in all nine passes (the first two 20;
-// passes with nothing to do 2 to 4 us), where moving every element in every
-// pass took 40 us a pass.
+// 2^22 keys in 4096 segments take 27 us in all nine passes (the first, which
+// finishes all of them, 14; each of the others, whose work-groups read ext and
+// leave, 1.6), where moving every element in every pass took 40 us a pass.
 // Work-group (w, y) writes outputs [w*C, w*C + C) (C = kSortTile) as far as
 // they belong to the head (y = 0) or tail (1) segment of its block: the first
 // two wavefronts find where the chunk's ends cross the merge path (64 probes
