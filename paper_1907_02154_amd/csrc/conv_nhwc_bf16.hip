@@ -1397,7 +1397,8 @@ __global__ __launch_bounds__(64 * WPX * WCH) void igemm_bf16_halo_cl_kernel(Conv
 // each of the first seven taps; it waits for both at the end of its next
 // reading phase.
 //   What bounds it: the reading phase.  Its 64 KB of operands and 20 KB of
-// incoming requests take about 770 cycles of LDS, beside the MFMAs' 512; a
+// incoming requests take about 730 cycles of LDS (660 at 128 bytes a cycle, and
+// 73 of bank conflicts, counted), beside the MFMAs' 512; a
 // chunk measures 0.42 us (880 cycles), plus 10 us a launch for the first
 // patch, the epilogue and the filter pack.  The wavefront that reads is alone
 // with its instructions, so the addresses of the next phase are computed

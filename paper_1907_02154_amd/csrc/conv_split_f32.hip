@@ -30,10 +30,11 @@
 //
 // Bound by the bf16 MFMA rate and by how evenly the tiles fill the CUs: VGG-16
 // 256 -> 256 3x3 at 56x56, batch 8 (29.6 GFLOP): 302 us on the fp32 MFMA
-// kernel, 178 us here, 13 us of it the split copy of x (4.9 TB/s); MFMAs busy
-// 60% of the cycles of a CU with two work-groups (392 tiles on 256 CUs, 46%
-// over all), no LDS bank conflicts.  Three stages of 16-channel chunks leave
-// two work-groups per CU; five stages (one fewer) were slower on every shape.
+// kernel, 178 us here, 13 us of it the split copy of x (4.9 TB/s).  Counted:
+// MFMAs busy 49% of the cycles of all SIMDs (392 tiles in 512 places; 56% at
+// 28x28, 980 work-groups), no LDS bank conflicts (64 x 128 tiles: 6 cycles per
+// 100 LDS instructions).  Three stages of 16-channel chunks leave two
+// work-groups per CU; five stages (one fewer) were slower on every shape.
 //
 // Both operands are split at 2^24 times their value and the sums scaled back,
 // so that no part of any fp32 value, subnormal ones included, falls below
