@@ -12,9 +12,13 @@
 // 16 taps replace eight fp32 MFMAs of 2 taps: 192 cycles per 32 x 32 x 16 block
 // instead of 512.
 // xh wh goes to one fp32 accumulator and the five small products to another,
-// so the roundings of the small ones do not add to the large sum's: against
-// 64 bits the result is no further off than the fp32 MFMA kernel's (measured
-// in the tests on every declared range).
+// so the roundings of the small ones do not add to the large sum's: in the
+// 2-norm against 64 bits the result is no further off than the fp32 MFMA
+// kernel's (0.31 to 0.92 of its error on 100 drawn layers).  As one accumulator
+// takes the whole reduction, of which that kernel's wavefronts hold an eighth
+// each, the error grows more with an output's size: outputs beyond twice the
+// rms are 1.1 to 1.6 times as far off as there, at most 1.6e-7 of the sum of
+// magnitudes (0.8e-7 there).
 //
 // A call
 //  1. splits x into a channel-last copy xs [N*H*W][groups][CB][3][16] (CB
