@@ -168,6 +168,10 @@ long conv2d_workspace_bytes(int N, int C, int H, int W, int K, int R, int S, int
  * (fp32 partial sums, reduced in a fixed order: results are run-to-run
  * deterministic), stage x channel-last (bf16) and pack the filters into the
  * order its kernel reads, all inside `ws`: the fastest single-call plans.
+ * Large fp32 layers (here, in conv2d_fwd_noalloc and in a stack) may run on the
+ * bf16 matrix cores with every value split into three bf16 parts, six products
+ * of parts for each product: fp32's precision over fp32's whole range,
+ * infinities and NaNs as without the split.
  * The library keeps no reference to ws after the call's kernels are
  * enqueued; they use it until they complete on `stream`, so concurrent calls
  * need distinct workspaces.  A workspace below conv2d_workspace_bytes that
